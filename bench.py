@@ -31,6 +31,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_TFLOPS = {"f16": 2500.0, "f32": 157.3}   # MI355X dense matrix peaks (fp16 = bf16 rate)
+PREFIX_DIMS = 16                               # features the prefix scan contracts for every pair
 METRIC = "certified lookups/s and query·entry pairs/s at N=1M cache, d=256, C=200"
 
 
@@ -173,7 +174,7 @@ def stream_bench(args, cfg) -> int:
     for t in range(cfg.rounds):
         zq = zq0 if t == 0 else g(queries(t))
         n_t = cache.n
-        pruned_t = args.prune and cache.lookup_prunes(args.precision)
+        pruned_t = takes_prefix_scan(cache, B, args)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         torch.cuda.synchronize()
         ts = time.perf_counter()
@@ -189,7 +190,7 @@ def stream_bench(args, cfg) -> int:
         rounds.append({"round": t, "n": n_t, "round_ms": dt * 1e3, "lookup_ms": lk, "hits": hits, "inserted": ins})
         total_s += dt
         total_lk += lk * 1e-3
-        flops += 2.0 * B * n_t * (32 if pruned_t else d)
+        flops += 2.0 * B * n_t * (PREFIX_DIMS if pruned_t else d)
         log(f"round {t}: n={n_t} round {dt * 1e3:.2f} ms lookup {lk:.2f} ms hits {hits}/{B} inserted {ins}")
     achieved = flops / total_lk / 1e12
     peak = PEAK_TFLOPS[args.precision]
@@ -210,7 +211,7 @@ def stream_bench(args, cfg) -> int:
         "config": {"workload": cfg.name, "N": N, "B": B, "d": d, "C": C, "store": cfg.store_dtype,
                    "rounds": cfg.rounds, "precision": args.precision,
                    "step": "one round: lookup+certify(B)+insert(misses)",
-                   "lookup": "pruned (LIPCACHE_LOOKUP_PRUNE)" if args.prune else "full"},
+                   "lookup": "prefix scan + exact re-check" if pruned_t else "full contraction + exact re-check"},
         "pairs_per_s": pairs / total_s,
         "lookup_pairs_per_s": pairs / total_lk,
         "final_n": cache.n,
@@ -218,10 +219,10 @@ def stream_bench(args, cfg) -> int:
         "rounds": rounds,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None,
-                     "kernel": "lookup_dma_kernel (fused contraction + filter + re-check)",
-                     "algorithmic": (f"sum over rounds of 2*B*n_t*d = {flops:.4e} flop" if not args.prune else
-                                     f"sum over rounds of the prefix contraction 2*B*n_t*32 = {flops:.4e} flop "
-                                     "(pruned lookup)")},
+                     "kernel": "lookup_prefix_kernel" if pruned_t else "lookup_dma_kernel",
+                     "algorithmic": (f"sum over rounds of 2*B*n_t*d = {flops:.4e} flop" if not pruned_t else
+                                     f"sum over rounds of the prefix contraction 2*B*n_t*{PREFIX_DIMS} = "
+                                     f"{flops:.4e} flop")},
         "cpu_baseline": None,
     }
     if not args.no_cpu_baseline:
@@ -473,9 +474,9 @@ def main() -> int:
     ap.add_argument("--index-k", type=int, default=256, metavar="K",
                     help="also run the batch through a K-cluster index after the timed steps (0: skip)")
     ap.add_argument("--prune", action="store_true",
-                    help="time the step with the pruned lookup (LIPCACHE_LOOKUP_PRUNE; same answers)")
+                    help="ask for the prefix scan (LIPCACHE_LOOKUP_PRUNE; large lookups take it by themselves)")
     ap.add_argument("--no-prune-context", action="store_true",
-                    help="skip timing the pruned lookup of the batch after the timed steps")
+                    help="skip timing the full contraction of the batch after the timed steps")
     ap.add_argument("--boundaries", action="store_true",
                     help="compare reuse boundaries (hit rate, certified-consistency rate) on the workload")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="MIB",
@@ -590,12 +591,12 @@ def main() -> int:
     log(f"{args.steps} steps in {elapsed:.3f} s; lookup {lk:.3f} ms avg (min {min(lk_ms):.3f}); "
         f"hits {hits}/{B}; rechecked {stats[1]}; band pairs {stats[2]}; inserted/step {inserted[-1]}")
 
-    pruned_path = args.prune and cache.lookup_prunes(args.precision)
+    pruned_path = takes_prefix_scan(cache, B, args)
     flops = 2.0 * B * n0 * d
     if pruned_path:
-        # the matrix work every pair gets: the first 32 features (blocks the
-        # prefix filter keeps also run the rest of the contraction)
-        flops = 2.0 * B * n0 * 32
+        # the matrix work every pair gets: the first 16 features (the pairs
+        # the prefix filter keeps are re-checked over all of them)
+        flops = 2.0 * B * n0 * PREFIX_DIMS
     achieved = flops / (lk * 1e-3) / 1e12
     peak = PEAK_TFLOPS[args.precision]
     out = {
@@ -622,9 +623,11 @@ def main() -> int:
         "cache_build_ms": t_build * 1e3,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None,
-                     "kernel": "lookup_dma_kernel (fused contraction + filter + re-check)",
+                     "kernel": ("lookup_prefix_kernel (exact prefix filter + re-check of what passes)" if pruned_path
+                                else "lookup_dma_kernel (fused contraction + filter + re-check)"),
                      "algorithmic": (f"2*B*N*d = {flops:.4e} flop per launch" if not pruned_path else
-                                     f"prefix contraction 2*B*N*32 = {flops:.4e} flop per launch (pruned lookup)")},
+                                     f"prefix contraction 2*B*N*{PREFIX_DIMS} = {flops:.4e} flop per launch "
+                                     "(every pair is ruled out by its distance over 16 features or re-checked)")},
         "cpu_baseline": None,
     }
     tr = measured_traffic(cfg.name, args.precision)
@@ -638,15 +641,13 @@ def main() -> int:
         out["roofline"]["hbm_gbs"] = tr["traffic_bytes"] / (lk * 1e-3) / 1e9
     else:
         out["roofline"]["traffic_source"] = "none: no counter profile of the current lookup.hip is committed"
-    if args.prune:
-        out["config"]["lookup"] = ("pruned (LIPCACHE_LOOKUP_PRUNE)" if pruned_path else
-                                   "LIPCACHE_LOOKUP_PRUNE requested; this cache takes the full path")
-    elif not args.no_prune_context:
+    out["config"]["lookup"] = "prefix scan + exact re-check" if pruned_path else "full contraction + exact re-check"
+    if pruned_path and not args.no_prune_context:
         try:
-            out["pruned_lookup"] = pruned_context(cache, zq, res, lk, args)
+            out["full_contraction"] = full_contraction_context(cache, zq, res, lk, args)
         except Exception as e:  # context only: report it, keep the headline line
-            log(f"pruned lookup context failed: {e}")
-            out["pruned_lookup"] = {"error": str(e)}
+            log(f"full contraction context failed: {e}")
+            out["full_contraction"] = {"error": str(e)}
     if args.index_k > 0:
         try:
             out["indexed_lookup"] = indexed_context(cache, zq, res, args)
@@ -659,35 +660,56 @@ def main() -> int:
     return 0
 
 
-def pruned_context(cache, zq, res, full_ms, args) -> dict:
-    """The same batch through the pruned lookup (LIPCACHE_LOOKUP_PRUNE; outside
-    the timed steps): HIP-event time of the call and whether every answer
-    equals the full lookup's.  Context for the headline, which stays the full
-    contraction of every pair."""
+def takes_prefix_scan(cache, B, args) -> bool:
+    """Whether ``cache.lookup`` of B queries takes the prefix scan: on request,
+    or by itself for a large enough float16 lookup (LIPCACHE_LOOKUP_PRUNE)."""
+    large = (B + 511) // 512 * 512 * cache.n * (cache.d - 32) >= 1 << 33
+    return args.precision == "f16" and cache.lookup_prunes("f16") and (args.prune or large)
+
+
+def full_contraction_context(cache, zq, res, prefix_ms, args) -> dict:
+    """The same batch on the plain workspace, where the lookup contracts every
+    pair over all d features (outside the timed steps): HIP-event time of the
+    call, its matrix rate, and whether every answer equals the timed ones."""
+    import ctypes
+
     import numpy as np
     import torch
 
-    out_p = cache.lookup(zq, precision=args.precision, prune=True)
+    from paper_2608_13144_amd import _lib, api
+
+    lib, B, prec = _lib.load(), zq.shape[0], _lib.F16
+    need = lib.lipcache_lookup_workspace_bytes(B, cache.n, cache.d, prec)
+    ws = torch.empty(need, dtype=torch.uint8, device=zq.device)
+    o = api.LookupResult(*(torch.empty_like(t) for t in (res.label, res.index, res.dist2, res.stats, res.band)))
+    p = [ctypes.c_void_p(t.data_ptr()) for t in (zq, o.label, o.index, o.dist2, o.stats, o.band, ws)]
+    cs = cache.cstruct()
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+    def call():
+        _lib.check("lipcache_lookup", lib.lipcache_lookup(ctypes.byref(cs), p[0], B, prec, *p[1:], need, stream))
+
+    call()
     torch.cuda.synchronize()
-    same = all(torch.equal(getattr(res, f).view(torch.uint8), getattr(out_p, f).view(torch.uint8))
+    same = all(torch.equal(getattr(res, f).view(torch.uint8), getattr(o, f).view(torch.uint8))
                for f in ("label", "index", "dist2", "band"))
-    sf, sp = res.stats.cpu().tolist(), out_p.stats.cpu().tolist()
+    sf, sp = o.stats.cpu().tolist(), res.stats.cpu().tolist()
     same = same and sf[0] == sp[0] and sf[2] == sp[2] and sf[3] == sp[3]
     ts = []
     for _ in range(10):
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
-        cache.lookup(zq, precision=args.precision, out=out_p, prune=True)
+        call()
         e1.record()
         torch.cuda.synchronize()
         ts.append(e0.elapsed_time(e1))
     ms = float(np.median(ts))
-    B = zq.shape[0]
-    log(f"pruned lookup: {ms:.3f} ms ({full_ms / ms:.2f}x the full lookup), same answers: {same}, "
-        f"re-checked pairs {sp[1]} (full {sf[1]})")
-    return {"lookup_ms": ms, "lookups_per_s": B / (ms * 1e-3), "pairs_per_s": B * cache.n / (ms * 1e-3),
-            "speedup_vs_full_lookup": full_ms / ms, "same_answers_as_full": bool(same),
-            "rechecked_pairs": int(sp[1]), "rechecked_pairs_full": int(sf[1])}
+    tflops = 2.0 * B * cache.n * cache.d / (ms * 1e-3) / 1e12
+    log(f"full contraction: {ms:.3f} ms ({tflops:.0f} TFLOP/s), same answers: {same}, "
+        f"re-checked pairs {sf[1]} (prefix scan {sp[1]})")
+    return {"lookup_ms": ms, "lookups_per_s": B / (ms * 1e-3), "tflops": tflops,
+            "frac_of_peak": tflops / PEAK_TFLOPS["f16"], "prefix_scan_speedup": ms / prefix_ms,
+            "same_answers": bool(same), "rechecked_pairs": int(sf[1]), "rechecked_pairs_prefix_scan": int(sp[1])}
 
 
 def indexed_context(cache, zq, res, args) -> dict:

@@ -61,18 +61,24 @@ typedef enum lipcache_status {
 enum { LIPCACHE_F32 = 0, LIPCACHE_BF16 = 1, LIPCACHE_F16 = 2 };
 
 /* Lookup option, ORed into `precision` (LIPCACHE_F16 | LIPCACHE_LOOKUP_PRUNE):
- * prefix pruning.  The squared distance over the first 32 features is a
- * lower bound of the full one (Eq. (13) sums non-negative terms), so a block
- * of query-entry pairs whose prefix filter (the same rigorous slack, with
- * the ball widened to r_i (1 + 3e-5) so that every pair of the boundary
- * band survives) rejects every pair cannot hold a hit or a band pair, and
- * the rest of its contraction is skipped.  Every output equals the lookup
- * without the option except stats[LIPCACHE_STAT_RECHECKED], which counts
- * fewer pairs the filter let through that were not hits.  Applies to the
- * float16 filter with 64 <= d <= 512 on caches of n >= 32768 rows with a
- * float16 image (other cases run the full contraction, with the same
- * answers); the workspace grows by about
- * 4 B + 4 n bytes (the entry thresholds padded to a multiple of 1024 rows). */
+ * prefix pruning.  The squared distance over the first 16 features is a
+ * lower bound of the full one (Eq. (13) sums non-negative terms), so a pair
+ * whose prefix filter (the same rigorous slack, with the ball widened to
+ * r_i (1 + 3e-5) so that every pair of the boundary band survives) rejects
+ * it is neither a hit nor a band pair, and its contraction is skipped; the
+ * pairs it keeps go through the full filter and the re-check.  Where it keeps
+ * too many to pay, the rest of the slice runs the full contraction.  Every
+ * output equals the full contraction's except
+ * stats[LIPCACHE_STAT_RECHECKED], which counts fewer pairs the full filter
+ * let through that were not hits.  Applies to the float16 filter with
+ * 64 <= d <= 512 on caches of n >= 32768 rows with a float16 image (other
+ * cases give the same answers with or without it); the workspace grows by
+ * about 4 B + 4 n bytes (the entry thresholds padded to a multiple of 1024
+ * rows).  A lookup without the option takes the same path by itself when
+ * the cache is as above (any d >= 64), the lookup is large enough to gain
+ * ((B rounded up to 512) n (d - 32) >= 2^33) and ws_bytes is at least the
+ * option's workspace size; with the plain size it runs the full
+ * contraction. */
 #define LIPCACHE_LOOKUP_PRUNE 0x100
 
 /* Radius modes (policy component rho, Sec. 4.3): the conservative radius of
@@ -100,7 +106,8 @@ enum {
 /* Indices of the lookup statistics counters (uint64_t stats[4]). */
 enum {
   LIPCACHE_STAT_HITS = 0,        /* queries with a non-empty hit set                   */
-  LIPCACHE_STAT_RECHECKED = 1,   /* (query, entry) pairs the exact re-check evaluated  */
+  LIPCACHE_STAT_RECHECKED = 1,   /* (query, entry) pairs the exact re-check evaluated
+                                    (see LIPCACHE_LOOKUP_PRUNE)                        */
   LIPCACHE_STAT_BAND_PAIRS = 2,  /* re-checked pairs with |D - r| <= 1e-5 r            */
   LIPCACHE_STAT_BAND_QUERIES = 3 /* queries with at least one such pair                */
 };
@@ -220,10 +227,10 @@ lipcache_status lipcache_lookup(const lipcache_cache* c, const float* zq, int64_
                                 void* ws, size_t ws_bytes, lipcache_stream_t stream);
 size_t lipcache_lookup_workspace_bytes(int64_t B, int64_t N, int32_t d, int32_t precision);
 
-/* 1 if lipcache_lookup(c, ..., precision, ...) takes the pruned path of
- * LIPCACHE_LOOKUP_PRUNE for this cache (float16 filter with a float16
- * image, 64 <= d <= 512, n >= 32768), 0 if it runs the full contraction
- * (always the case without the option, or for an invalid argument).  Host
+/* 1 if the option LIPCACHE_LOOKUP_PRUNE in `precision` applies to this cache
+ * (float16 filter with a float16 image, 64 <= d <= 512, n >= 32768), 0 if
+ * it does not, is not set, or an argument is invalid.  (Without the option
+ * a large lookup may take the same path: see LIPCACHE_LOOKUP_PRUNE.)  Host
  * only. */
 int32_t lipcache_lookup_prunes(const lipcache_cache* c, int32_t precision);
 

@@ -42,6 +42,9 @@
 //    filter often: each wave queues them in LDS, hands the queue to the
 //    global queue after its last tile in one reservation; waves past the
 //    list end only copy;
+//  - large lookups with a float16 image first scan the first 16 features of
+//    every row (lookup_prefix_kernel, below) and re-check what passes; the
+//    full kernel then takes only the slices where that tells too little;
 //  - recheck_queue_kernel settles the global queue chip-wide; a pair that
 //    finds the queue full is re-checked by its wave at once (same order of
 //    sums, so the same d^2 either way).
@@ -88,10 +91,18 @@ struct LookupParams {
   double eta1;           // absolute slack per unit of ||z_i||
   double range2;         // ||z_i||^2 from which an entry passes against everything
   const float* athr;     // [n_pad] per-entry filter thresholds A_i (+inf past n)
-  // Prefix pruning: thresholds of the filter over features 0..31 (Q'_q per
-  // query, A'_i per entry, +inf past n); null without the option.
+  // Prefix scan: thresholds of the filter over features 0..kPrefixDims-1
+  // (Q'_q per query, A'_i per entry, +inf past n); null in the other scans.
   const float* qthr_p;
   const float* athr_p;
+  // Slices the prefix scan hands to the full contraction: one list per XCD
+  // of (first query, slice, row to resume at), dn_cap slots each, dn_count
+  // entries reserved; pf_qblock is the prefix scan's query block.
+  int64_t* dn_work;
+  int64_t* dn_row;
+  unsigned long long* dn_count;
+  int64_t dn_cap;
+  int pf_qblock;
   const void* cimg;      // rows streamed by the DMA kernel (float16 image or z)
   int n_qblocks;
   int64_t slice_len;
@@ -120,6 +131,7 @@ struct LookupParams {
   int64_t* gq_e;
   unsigned long long* gq_count;
   int64_t gq_cap;
+  bool near_only;        // see RecheckArgs
 };
 
 // ------------------------------------------------------------- prep
@@ -153,15 +165,15 @@ __device__ __forceinline__ float entry_threshold(float rr, float n2f, double kap
   return f32_round_down((kappa_c * n2 - r2) * 0.5 - eta1 * __builtin_sqrt(n2) - 0.5 * kFilterAbsSlack);
 }
 
-// Prefix filter (features 0..kPrefixDims-1, the first float16 k-step).  The
-// prefix of a squared distance is a lower bound of the whole, so a pair with
-// ||q - z_i|| < r_i (a hit) or within the boundary band has a prefix below
-// r_i^2 (1 + 1e-5)^2 < r_i^2 (1 + 3e-5); the thresholds are those of the
-// full filter with d_pad = kPrefixDims, the prefix norms, and that widened
-// ball, so such a pair always passes.  A row whose full squared norm
-// reaches range2 passes (as in the full filter); a NaN or infinite query
+// Prefix filter (features 0..kPrefixDims-1, one k-step of the 32x32 matrix
+// instruction).  The prefix of a squared distance is a lower bound of the
+// whole, so a pair with ||q - z_i|| < r_i (a hit) or within the boundary band
+// has a prefix below r_i^2 (1 + 1e-5)^2 < r_i^2 (1 + 3e-5); the thresholds are
+// those of the full filter with d_pad = kPrefixDims, the prefix norms, and
+// that widened ball, so such a pair always passes.  A row whose full squared
+// norm reaches range2 passes (as in the full filter); a NaN or infinite query
 // norm never does (it has no hit).
-constexpr int kPrefixDims = 32;
+constexpr int kPrefixDims = 16;
 constexpr double kPrefixBand = 3e-5;
 
 __device__ __forceinline__ float prefix_query_threshold(double s, double sp, const Thresholds& t) {
@@ -170,41 +182,43 @@ __device__ __forceinline__ float prefix_query_threshold(double s, double sp, con
   return f32_round_down(t.kq * sp * 0.5 - t.eta1 * __builtin_sqrt(sp) - t.eta0);
 }
 
-__device__ __forceinline__ float prefix_entry_threshold(float rr, float n2f, double n2p, const Thresholds& t) {
+// A'_i from the image's prefix norm s = ||f16(z_P)||^2 (the image is what the
+// scan streams: 32 bytes a row where the stored float32 prefix has 64).  Each
+// image value is z_k (1 + e) + t with |e| <= u and |t| <= 2^-14, so
+//   (sqrt(s) - 4 2^-14) / (1 + u) <= ||z_P|| <= (sqrt(s) + 4 2^-14) / (1 - u);
+// the lower bound goes into the term that grows with the norm and the upper
+// one into the slack.  u = 0 for a bf16 store, exact in float16 above the
+// sub-normals.  Rows the image clamps have a norm past range2.
+struct PrefixNorm {
+  double lo;  // 1 / (1 + u), rounded down
+  double hi;  // 1 / (1 - u), rounded up
+};
+constexpr double kPrefixEta = 4.0 / 16384.0;  // sqrt(kPrefixDims) 2^-14
+
+__device__ __forceinline__ float prefix_entry_threshold(float rr, float n2f, double s, const Thresholds& t,
+                                                        const PrefixNorm& pn) {
   if (!(rr > 0.0f)) return __builtin_inff();
   const double n2 = static_cast<double>(n2f);
   if (n2 >= t.range2 && n2 < __builtin_inf()) return kPassAll;
   const double r2 = static_cast<double>(rr) * static_cast<double>(rr) * (1.0 + kPrefixBand);
-  return f32_round_down((t.kappa_c * n2p - r2) * 0.5 - t.eta1 * __builtin_sqrt(n2p) - 0.5 * kFilterAbsSlack);
+  const double h = __builtin_sqrt(s);
+  const double lo = h > kPrefixEta ? (h - kPrefixEta) * pn.lo : 0.0;
+  const double hi = (h + kPrefixEta) * pn.hi;
+  return f32_round_down((t.kappa_c * lo * lo - r2) * 0.5 - t.eta1 * hi - 0.5 * kFilterAbsSlack);
 }
 
-// Squared norm of the first kPrefixDims stored features of row i, in float64.
-__device__ __forceinline__ double prefix_norm2(const void* cz, int store, int d, int64_t i) {
+// Squared norm of the first kPrefixDims image values of row i, in float64.
+__device__ __forceinline__ double prefix_norm2(const void* img, int d, int64_t i) {
+  const uint4* row = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(img) + i * d);
+  const uint4 v0 = row[0], v1 = row[1];
+  const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
   double s = 0.0;
-  if (store == LIPCACHE_BF16) {
-    const uint4* row = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(cz) + i * d);
 #pragma unroll
-    for (int c = 0; c < kPrefixDims / 8; ++c) {
-      const uint4 v = row[c];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const double lo = static_cast<double>(__builtin_bit_cast(float, w[j] << 16));
-        const double hi = static_cast<double>(__builtin_bit_cast(float, w[j] & 0xffff0000u));
-        s = __builtin_fma(lo, lo, s);
-        s = __builtin_fma(hi, hi, s);
-      }
-    }
-  } else {
-    const float4* row = reinterpret_cast<const float4*>(static_cast<const float*>(cz) + i * d);
-#pragma unroll
-    for (int c = 0; c < kPrefixDims / 4; ++c) {
-      const float4 v = row[c];
-      s = __builtin_fma(static_cast<double>(v.x), static_cast<double>(v.x), s);
-      s = __builtin_fma(static_cast<double>(v.y), static_cast<double>(v.y), s);
-      s = __builtin_fma(static_cast<double>(v.z), static_cast<double>(v.z), s);
-      s = __builtin_fma(static_cast<double>(v.w), static_cast<double>(v.w), s);
-    }
+  for (int j = 0; j < 8; ++j) {
+    const double lo = static_cast<double>(f16_to_f32(static_cast<uint16_t>(w[j])));
+    const double hi = static_cast<double>(f16_to_f32(static_cast<uint16_t>(w[j] >> 16)));
+    s = __builtin_fma(lo, lo, s);
+    s = __builtin_fma(hi, hi, s);
   }
   return s;
 }
@@ -227,14 +241,15 @@ struct PrepEntries {
   unsigned long long* gq_count;  // emptied for the scan that follows (nullable)
   double* qnorm;                 // ||q||^2 in float64 of every query (nullable)
   uint16_t* zq16;                // float16 copy of the queries (nullable)
-  // prefix pruning (qthr_p == nullptr: off): Q'_q, A'_i [np_pad] and their
-  // constants
+  // prefix scan (qthr_p == nullptr: off): Q'_q, A'_i [np_pad], their
+  // constants, the image, and the counters of its lists to clear
   float* qthr_p;
   float* athr_p;
   int64_t np_pad;
-  const void* cz;
-  int store;
+  const void* cimg;
   Thresholds tp;
+  PrefixNorm pn;
+  unsigned long long* dn_count;
 };
 
 // Blocks [0, qblocks): one wave per query, Q_q, reset of the per-query state
@@ -248,13 +263,14 @@ __global__ void lookup_prep_kernel(const float* __restrict__ zq, int64_t B, int 
     const int64_t i = static_cast<int64_t>(blockIdx.x - qblocks) * kLkThreads + threadIdx.x;
     write_athr(i, pe.cr, pe.cnorm2, pe.n, pe.n_pad, t.kappa_c, t.eta1, t.range2, pe.athr);
     if (pe.athr_p && i < pe.np_pad)
-      pe.athr_p[i] = i < pe.n ? prefix_entry_threshold(pe.cr[i], pe.cnorm2[i], prefix_norm2(pe.cz, pe.store, d, i), pe.tp)
+      pe.athr_p[i] = i < pe.n ? prefix_entry_threshold(pe.cr[i], pe.cnorm2[i], prefix_norm2(pe.cimg, d, i), pe.tp, pe.pn)
                               : __builtin_inff();
     return;
   }
   const int64_t q = static_cast<int64_t>(blockIdx.x) * kLkWaves + threadIdx.x / kWave;
   if (blockIdx.x == 0 && threadIdx.x < 4) stats[threadIdx.x] = 0;
   if (blockIdx.x == 0 && threadIdx.x == 4 && pe.gq_count) *pe.gq_count = 0ull;
+  if (blockIdx.x == 0 && threadIdx.x < kXcds && pe.dn_count) pe.dn_count[threadIdx.x] = 0ull;
   if (q >= B) return;
   const float* row = zq + q * d;
   double s = 0.0, sp = 0.0;
@@ -334,6 +350,24 @@ __device__ __forceinline__ void block_work(const LookupParams& p, int64_t qblock
   qend = p.B;
   e_begin = static_cast<int64_t>(slice) * p.slice_len;
   e_end = e_begin + p.slice_len < p.n ? e_begin + p.slice_len : p.n;
+}
+
+// The full kernel behind a prefix scan: turn `it` of a block over its XCD's
+// list of slices (the list keeps a slice on the XCD that scans it), each
+// split into the kernel's own query blocks.  False past the list's end.
+__device__ __forceinline__ bool dense_work(const LookupParams& p, int qblock, int64_t it, int64_t& q0,
+                                           int64_t& e_begin, int64_t& e_end) {
+  const int xcd = static_cast<int>(blockIdx.x) % kXcds;
+  const int split = p.pf_qblock > qblock ? p.pf_qblock / qblock : 1;
+  const int64_t item = it / split;
+  if (item >= static_cast<int64_t>(p.dn_count[xcd])) return false;
+  const int64_t w = p.dn_work[xcd * p.dn_cap + item];
+  q0 = (w >> 24) + (it % split) * qblock;
+  e_begin = p.dn_row[xcd * p.dn_cap + item];
+  e_end = ((w & 0xffffff) + 1) * p.slice_len;
+  e_end = e_end < p.n ? e_end : p.n;
+  if (q0 >= p.B) e_end = e_begin;
+  return true;
 }
 
 // The query at position j of the block's range.
@@ -438,10 +472,18 @@ struct RecheckArgs {
   const int64_t* emap;
   int64_t eoff;
   const int32_t* qlist;
+  // Prefix scan, pairs that find the queue full: count as re-checked only
+  // those that prove to lie in the widened ball (the full filter passes every
+  // one of them, so the count stays at most the full contraction's).
+  bool near_only;
 };
 
 __device__ __forceinline__ RecheckArgs recheck_args(const LookupParams& p, int64_t qend, const int32_t* qlist) {
-  return RecheckArgs{p.zq, p.cz, p.cr, p.best, p.bflag, p.stats, qend, p.n, p.d, p.emap, p.eoff, qlist};
+  return RecheckArgs{p.zq, p.cz, p.cr, p.best, p.bflag, p.stats, qend, p.n, p.d, p.emap, p.eoff, qlist, p.near_only};
+}
+
+__device__ __forceinline__ bool counts(bool near_only, double d2, double r) {
+  return !near_only || d2 <= r * r * (1.0 + kPrefixBand);
 }
 
 // ||q - z_e||^2 of query row q and cache row e in float64 over the whole
@@ -461,8 +503,8 @@ __device__ __forceinline__ double wave_dist2(const RecheckArgs& p, int64_t q, in
 // Outcome of one re-checked pair (one lane): counters, band flag, and the
 // packed (d^2, entry) key of a hit into the query's minimum.
 __device__ __forceinline__ void record_pair(const RecheckArgs& p, int64_t q, int64_t e, double d2) {
-  atomicAdd(&p.stats[LIPCACHE_STAT_RECHECKED], 1ull);
   const double r = static_cast<double>(p.cr[e]);
+  if (counts(p.near_only, d2, r)) atomicAdd(&p.stats[LIPCACHE_STAT_RECHECKED], 1ull);
   const bool hit = d2 < r * r;
   if (__builtin_fabs(__builtin_sqrt(d2) - r) <= 1e-5 * r) {
     atomicAdd(&p.stats[LIPCACHE_STAT_BAND_PAIRS], 1ull);
@@ -477,9 +519,21 @@ __device__ __forceinline__ void record_pair(const RecheckArgs& p, int64_t q, int
   }
 }
 
-// Exact re-check of the pairs whose bits are set in `mask` (bit rt*4+i of a
-// lane = accumulator i of row tile rt), one pair at a time by the whole wave.
-template <int SRC>
+// Bit b of lane `lane`'s pair mask: which query row of the wave's row tiles,
+// and which cache row of the column tile.  TILE = 16: bit rt*4+i is
+// accumulator i of 16-row tile rt; TILE = 32: bit rt*16+i of 32-row tile rt
+// (the 32x32 output keeps four rows per group of eight).
+template <int TILE>
+__device__ __forceinline__ int mask_row(int bit, int lane) {
+  if constexpr (TILE == 16) return (bit >> 2) * 16 + 4 * (lane >> 4) + (bit & 3);
+  return (bit >> 4) * 32 + 8 * ((bit >> 2) & 3) + 4 * (lane >> 5) + (bit & 3);
+}
+template <int TILE>
+__device__ __forceinline__ int mask_col(int lane) { return lane & (TILE - 1); }
+
+// Exact re-check of the pairs whose bits are set in `mask` (see mask_row),
+// one pair at a time by the whole wave.
+template <int SRC, int TILE = 16>
 __device__ __noinline__ void recheck_pairs(const RecheckArgs p, uint32_t mask, int64_t qwave, int64_t ebase) {
   const int lane = lane_id();
   while (true) {
@@ -489,9 +543,8 @@ __device__ __noinline__ void recheck_pairs(const RecheckArgs p, uint32_t mask, i
     const uint32_t msrc = static_cast<uint32_t>(__shfl(static_cast<int>(mask), src, kWave));
     const int bit = __builtin_ctz(msrc);
     if (lane == src) mask &= mask - 1u;
-    const int rt = bit >> 2, i = bit & 3;
-    const int64_t qpos = qwave + rt * 16 + 4 * (src >> 4) + i;
-    const int64_t e = ebase + (src & 15);
+    const int64_t qpos = qwave + mask_row<TILE>(bit, src);
+    const int64_t e = ebase + mask_col<TILE>(src);
     if (qpos >= p.qend || e >= p.n) continue;  // padded rows never pass; kept as a guard
     const int64_t q = query_at(p.qlist, qpos);
     const double d2 = wave_dist2<SRC>(p, q, e);
@@ -561,15 +614,15 @@ __device__ __forceinline__ int settle_four(const RecheckArgs& p, bool valid, int
       acc[j] = __builtin_fma(diff, diff, acc[j]);
     }
   }
-  int done = 0;
+  bool counted = false;
 #pragma unroll
   for (int j = 0; j < P; ++j) {
-    done += v[j] ? 1 : 0;
     const double d2 = wave_sum(acc[j]);
     if (lane == j && v[j]) {
       // record_pair with the radius and key fetched above (the re-check
       // count is the caller's)
       const double r = static_cast<double>(mr);
+      counted = counts(p.near_only, d2, r);
       if (__builtin_fabs(__builtin_sqrt(d2) - r) <= 1e-5 * r) {
         atomicAdd(&p.stats[LIPCACHE_STAT_BAND_PAIRS], 1ull);
         atomicOr(&p.bflag[mq], 1u);
@@ -582,7 +635,7 @@ __device__ __forceinline__ int settle_four(const RecheckArgs& p, bool valid, int
       }
     }
   }
-  return done;
+  return __popcll(__ballot(counted));
 }
 
 template <int SRC>
@@ -633,12 +686,11 @@ __device__ __forceinline__ uint64_t lane0_u64(uint64_t v) {
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-// Slice mode: appends the pairs of `mask` (bit rt*4+i of lane (m16, g) =
-// query row 4g + i of row tile rt against entry ebase + m16) to the global
+// Slice mode: appends the pairs of `mask` (see mask_row) to the global
 // re-check queue, one pair per lane and pass with one reservation per pass.
 // Pairs that find no slot below the capacity are re-checked at once (a cold
 // path: the queue holds several pairs per query).
-template <int SRC>
+template <int SRC, int TILE = 16>
 __device__ __forceinline__ void enqueue_pairs(const LookupParams& lp, uint32_t mask, int64_t qwave, int64_t ebase,
                                               int64_t qend, const int32_t* qlist) {
   const int lane = lane_id();
@@ -656,15 +708,15 @@ __device__ __forceinline__ void enqueue_pairs(const LookupParams& lp, uint32_t m
       const uint64_t slot = base + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(bal >> 32),
                                                              __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u));
       if (slot < cap) {
-        lp.gq_pos[slot] = qwave + (bit >> 2) * 16 + 4 * (lane >> 4) + (bit & 3);
-        lp.gq_e[slot] = ebase + (lane & 15);
+        lp.gq_pos[slot] = qwave + mask_row<TILE>(bit, lane);
+        lp.gq_e[slot] = ebase + mask_col<TILE>(lane);
       } else {
         rest |= 1u << bit;
       }
       mask &= mask - 1u;
     }
   }
-  if (__ballot(rest != 0u) != 0ull) recheck_pairs<SRC>(recheck_args(lp, qend, qlist), rest, qwave, ebase);
+  if (__ballot(rest != 0u) != 0ull) recheck_pairs<SRC, TILE>(recheck_args(lp, qend, qlist), rest, qwave, ebase);
 }
 
 // Work-list mode: moves the wave's LDS queue to the global queue when it
@@ -718,8 +770,8 @@ __device__ __forceinline__ void queue_pairs(const RecheckArgs& p, RecheckQueue& 
       const int slot = rq.n + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
                                   static_cast<uint32_t>(bal >> 32),
                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u)));
-      rq.q[slot] = (bit >> 2) * 16 + 4 * (lane >> 4) + (bit & 3);
-      rq.e[slot] = ebase + (lane & 15);
+      rq.q[slot] = mask_row<16>(bit, lane);
+      rq.e[slot] = ebase + mask_col<16>(lane);
       mask &= mask - 1u;
     }
     rq.n += fresh;
@@ -765,7 +817,8 @@ __device__ __forceinline__ void load_queries(const LookupParams& p, const int32_
   }
 }
 
-template <int MODE, int SRC, int KS, int RT, bool DUMP, bool LIST>
+// DENSE: a fixed grid that works off the slices a prefix scan listed.
+template <int MODE, int SRC, int KS, int RT, bool DUMP, bool LIST, bool DENSE>
 __global__ __launch_bounds__(kLkThreads, 2) void lookup_kernel(const LookupParams p) {
   using T = ModeTraits<MODE>;
   constexpr int kDPad = KS * T::kPerStep;
@@ -775,14 +828,19 @@ __global__ __launch_bounds__(kLkThreads, 2) void lookup_kernel(const LookupParam
   __shared__ float athr[kTileN];
 
   int64_t q0, qend, e_begin, e_end;
-  block_work(p, kLkWaves * RT * 16, q0, qend, e_begin, e_end);
   const int32_t* qlist = LIST ? p.qlist : nullptr;
-  if constexpr (!LIST) qend = p.B;
-
   const int lane = lane_id();
   const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
   const int m16 = lane & 15;
   const int g = lane >> 4;
+
+  for (int64_t it = static_cast<int64_t>(blockIdx.x) / kXcds;; it += gridDim.x / kXcds) {
+  if constexpr (DENSE) {
+    if (!dense_work(p, kLkWaves * RT * 16, it, q0, e_begin, e_end)) return;
+  } else {
+    block_work(p, kLkWaves * RT * 16, q0, qend, e_begin, e_end);
+  }
+  if constexpr (!LIST) qend = p.B;
   const int64_t qwave = q0 + wave * (RT * 16);
 
   u32x4 a[RT][KS];
@@ -862,6 +920,8 @@ __global__ __launch_bounds__(kLkThreads, 2) void lookup_kernel(const LookupParam
         }
       }
     }
+  }
+  if constexpr (!DENSE) break;
   }
 }
 
@@ -1219,7 +1279,8 @@ __device__ __forceinline__ void compute_tile(const unsigned char* buf, const flo
 
 // NW waves per workgroup (8, or 4 with two workgroups per CU), two waves
 // per SIMD either way.
-template <int MODE, int STORE, int KS, int RT, int NW, bool DUMP, bool LIST>
+// DENSE: a fixed grid that works off the slices a prefix scan listed.
+template <int MODE, int STORE, int KS, int RT, int NW, bool DUMP, bool LIST, bool DENSE>
 __global__ __launch_bounds__(NW * kWave, 2) void lookup_dma_kernel(const LookupParams p) {
   using T = ModeTraits<MODE>;
   constexpr int kCPR = 4 * KS;
@@ -1233,17 +1294,24 @@ __global__ __launch_bounds__(NW * kWave, 2) void lookup_dma_kernel(const LookupP
   __shared__ int32_t rq_q[LIST ? NW * kRq : 1];
 
   int64_t q0, qend, e_begin, e_end;
-  block_work(p, NW * RT * 16, q0, qend, e_begin, e_end);
   const int32_t* qlist = LIST ? p.qlist : nullptr;
-  if constexpr (!LIST) qend = p.B;
-
   const int lane = lane_id();
   const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
   const int m16 = lane & 15;
   const int g = lane >> 4;
+
+  for (int64_t it = static_cast<int64_t>(blockIdx.x) / kXcds;; it += gridDim.x / kXcds) {
+  if constexpr (DENSE) {
+    if (!dense_work(p, NW * RT * 16, it, q0, e_begin, e_end)) return;
+    __syncthreads();  // the tiles of the turn before have been read
+    if (e_begin >= e_end) continue;
+  } else {
+    block_work(p, NW * RT * 16, q0, qend, e_begin, e_end);
+    if (e_begin >= e_end) return;  // whole workgroup: an empty slice
+  }
+  if constexpr (!LIST) qend = p.B;
   const int64_t qwave = q0 + wave * (RT * 16);
 
-  if (e_begin >= e_end) return;  // whole workgroup: an empty slice
   // Work-list mode: a wave whose queries all lie past the list's end only
   // moves its share of each tile (the copies and barriers are the block's).
   const bool active = !LIST || qwave < qend;
@@ -1278,210 +1346,359 @@ __global__ __launch_bounds__(NW * kWave, 2) void lookup_dma_kernel(const LookupP
   if constexpr (LIST) {
     if (active) flush_queue<STORE>(p, recheck_args(p, qend, qlist), rq, qwave);
   }
+  if constexpr (!DENSE) break;
+  }
 }
 
-// ------------------------------------------------------------- pruned scan
-// The pruned lookup (LIPCACHE_LOOKUP_PRUNE) streams only the prefix of every
-// row: 64 bytes (features 0..31 of the float16 image) per row, 1024 rows per
-// 64 KiB LDS tile, double-buffered, with the prefix thresholds A'_i of the
-// tile's rows.  Each 16-entry column tile gets k-step 0 only; the rare column
-// tiles where a pair passes the prefix filter are formed again from the
-// image in global memory, exactly as the full kernel forms them, and go
-// through the full filter and the re-check.
-constexpr int kPrRows = 1024;                 // rows per prefix tile
-constexpr int kPrSubs = kPrRows / kColTile;   // column tiles per prefix tile
+// ------------------------------------------------------------- prefix scan
+// Exact pruning of the contraction: the scan streams only the prefix of every
+// row (features 0..15 of the float16 image, 32 bytes a row) and forms one
+// k-step of v_mfma_f32_32x32x16_f16 per 32x32 block of pairs, accumulated onto
+// -Q'_q, so a block holds no hit and no boundary-band pair unless some
+// accumulator reaches A'_i.  The pairs that do go to the re-check queue.
+//
+// What bounds it: the vector pipe and the matrix pipe about equally.  A
+// 64-query wave spends 2 matrix instructions (64 cycles) and 17 vector ones
+// (68 cycles: one v_max3 per two accumulators and the compare) per 32-entry
+// column tile.  Sixteen features instead of 32 (16x16x32 instructions) halve
+// the matrix cycles and the LDS bytes per pair for the same vector work.  A
+// wave holds only the prefix of its queries, so four waves share a SIMD and
+// cover each other's matrix latency.
+//
+// Workgroup: 8 waves over tiles of 1,024 rows (32 KiB, double-buffered).  EW
+// of them share the same 64 queries and take every EW-th column tile: 1 for
+// batches past 256 queries, up to 8 for at most 64 queries, where the rows
+// are what there is to split.
+//
+// Where the prefix tells little (features that repeat, balls as wide as the
+// data) the re-checks would cost more than the full contraction: a re-checked
+// pair takes about as long as 1,500 contracted ones (0.5 ns against 0.33 ps a
+// pair over the whole chip at d = 256; both grow with d).  So the workgroup
+// counts the pairs that pass, and past one in 2,048 (32 per wave and tile) it
+// stops before settling the tile it is in and puts the rest of its slice on a
+// list, which the full kernel (same queue) works off right after.
+constexpr int kPrRows = 1024;               // rows per prefix tile
+constexpr int kPrCol = 32;                  // rows per column tile
+constexpr int kPrSubs = kPrRows / kPrCol;   // column tiles per prefix tile
+constexpr int kPrWaves = 8;
+constexpr int kPrThreads = kPrWaves * kWave;
+constexpr int kPrWaveQ = 64;                // queries per wave: two 32-row tiles
+constexpr int kPrRT = 2;
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ f32x16 mfma_prefix(u32x4 a, u32x4 b, f32x16 acc) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), acc, 0, 0,
+                                                0);
+}
 
 // Copies rows [t0, t0 + kPrRows) of the prefix into an LDS tile (rows past
-// e_end repeat its last row) and their thresholds A'_i.  Thread tid copies
-// chunk tid % 4 of rows tid / 4 + 128 j; in the tile, chunk c of row r sits
-// in slot c ^ swz(r) (the layout lds_operand<1> reads), and swz(r) =
-// (r / 4) % 4 is the same for all of a thread's rows.
+// n repeat the last row: their thresholds are +inf) and their thresholds
+// A'_i.  The tile holds 32-row groups of 1 KiB, the first 16-byte chunk of
+// the 32 rows and then the second: lane l reads its operand at 16 l.
 __device__ __forceinline__ void issue_prefix_tile(unsigned char* buf, float* athp_buf, const LookupParams& p,
-                                                  int64_t t0, int64_t e_end, int wave) {
-  constexpr int kThreads = kDmaWaves * kWave;
-  constexpr int kRowsPerIter = kThreads / 4;
-  constexpr int kIters = kPrRows / kRowsPerIter;
+                                                  int64_t t0, int wave) {
   const int row_bytes = p.d * 2;
-  const int tid = static_cast<int>(threadIdx.x);
-  const int r0 = tid / 4;
-  const int c = (tid % 4) ^ lds_swizzle<4>(r0);
+  const int lane = lane_id();
   const unsigned char* base = static_cast<const unsigned char*>(p.cimg) + t0 * static_cast<int64_t>(row_bytes);
-  if (e_end - t0 >= kPrRows) {
-    const uint32_t voff = static_cast<uint32_t>(r0 * row_bytes + c * 16);
+  const int64_t left = p.n - t0;
+  const int last = left < kPrRows ? static_cast<int>(left) - 1 : kPrRows - 1;
 #pragma unroll
-    for (int j = 0; j < kIters; ++j)
-      lds_copy<16>(base + static_cast<int64_t>(j * kRowsPerIter) * row_bytes, voff,
-                   buf + (j * kThreads + wave * kWave) * 16);
-  } else {
-    const int last = static_cast<int>(e_end - t0) - 1;
-#pragma unroll
-    for (int j = 0; j < kIters; ++j) {
-      const int row = j * kRowsPerIter + r0;
-      const int rr = row < last ? row : last;
-      lds_copy<16>(base, static_cast<uint32_t>(rr * row_bytes + c * 16), buf + (j * kThreads + wave * kWave) * 16);
-    }
+  for (int j = 0; j < kPrSubs / kPrWaves; ++j) {
+    const int group = j * kPrWaves + wave;
+    const int row = group * kPrCol + (lane & 31);
+    const int rr = row < last ? row : last;
+    lds_copy<16>(base, static_cast<uint32_t>(rr * row_bytes + (lane >> 5) * 16), buf + group * (kPrCol * 32));
   }
-  // thresholds: 1024 floats, two 64-float copies per wave (the array is
-  // padded with +inf past n by more than a tile)
 #pragma unroll
-  for (int i = 0; i < kPrRows / (kDmaWaves * kWave); ++i) {
-    const int w = wave * (kPrRows / (kDmaWaves * kWave)) + i;
-    lds_copy<4>(p.athr_p + t0 + w * kWave, static_cast<uint32_t>(lane_id() * 4),
+  for (int i = 0; i < kPrRows / kPrThreads; ++i) {
+    const int w = wave * (kPrRows / kPrThreads) + i;
+    lds_copy<4>(p.athr_p + t0 + w * kWave, static_cast<uint32_t>(lane * 4),
                 static_cast<unsigned char*>(static_cast<void*>(athp_buf)) + w * kWave * 4);
   }
 }
 
-// Rare path of the pruned scan: column tile `sub` of the prefix tile at t0
-// (rows e = t0 + 16 sub + m16, those at or past e_end never pass) formed as
-// the full kernel forms it, from the image in global memory, then the full
-// filter and the re-check.
-template <int STORE, int KS, int RT>
-__device__ __forceinline__ void prune_survivor(const LookupParams& p, int64_t t0, int sub, int64_t e_end,
-                                               int64_t qwave, int64_t qend, int m16, int g,
-                                               const u32x4 (&a)[RT][KS], RecheckQueue& rq) {
-  constexpr bool kFold = kFoldQ<kModeF16, KS>;
-  const int64_t ebase = t0 + static_cast<int64_t>(sub) * kColTile;
-  const int64_t e = ebase + m16;
-  const bool live = e < e_end;
-  const int64_t er = live ? e : e_end - 1;
-  f32x4 qf[RT];
-  load_thresholds<RT>(p.qthr, qwave, qend, nullptr, g, kFold, qf);
-  f32x4 acc[RT];
+// The pairs of one column tile that pass (bits as mask_row<32>), from the
+// tile's operand and thresholds.
+__device__ __forceinline__ uint32_t prefix_mask(u32x4 b, float an, const u32x4 (&a)[kPrRT], const f32x16 (&nq)[kPrRT]) {
+  uint32_t mask = 0u;
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) acc[rt] = kFold ? qf[rt] : f32x4{0.f, 0.f, 0.f, 0.f};
-  u32x4 b[KS];
+  for (int rt = 0; rt < kPrRT; ++rt) {
+    const f32x16 acc = mfma_prefix(a[rt], b, nq[rt]);
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) b[ks] = load_chunk<kModeF16, LIPCACHE_F16>(p.cimg, er, p.d, ks * 32 + g * 8);
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma_step<kModeF16>(a[rt][ks], b[ks], acc[rt]);
+    for (int i = 0; i < 16; ++i) mask |= static_cast<uint32_t>(acc[i] >= an) << (rt * 16 + i);
   }
-  f32x4 qt[RT];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) qt[rt] = kFold ? f32x4{0.f, 0.f, 0.f, 0.f} : qf[rt];
-  const float an = live ? p.athr[e] : __builtin_inff();
-  float mx = -__builtin_inff();
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) mx = __builtin_fmaxf(mx, acc[rt][i] - qt[rt][i]);
-  }
-  if (__ballot(mx >= an) != 0ull) filter_and_recheck<STORE, RT, false>(p, acc, qt, an, qwave, qend, nullptr, ebase, rq);
+  return mask;
 }
 
-// One prefix tile: k-step 0 of every column tile against the lane's 16
-// queries (accumulators started at -Q'_q: the test is max_16(acc) >= A'_i),
-// software-pipelined one column tile behind, with the operands read two
-// column tiles ahead; passing column tiles are marked in a wave-uniform
-// mask and formed again after the tile.  A partial tile (the end of a
-// slice) takes a plain loop that also masks rows past e_end.
-template <int STORE, int KS, int RT>
-__device__ __forceinline__ void prune_tile(const unsigned char* buf, const float* athp_buf, const LookupParams& p,
-                                           int64_t t0, int64_t e_end, int64_t qwave, int64_t qend, int m16, int g,
-                                           const u32x4 (&a)[RT][KS], const f32x4 (&nqp)[RT], RecheckQueue& rq) {
-  uint64_t pass = 0ull;
-  if (e_end - t0 >= kPrRows) {
-    u32x4 bq[2];
-    bq[0] = lds_operand<1>(buf, 0, 0, m16, g);
-    bq[1] = lds_operand<1>(buf, 1, 0, m16, g);
-    f32x4 pacc[RT];
-    float anp = 0.0f;
-#pragma unroll
-    for (int sub = 0; sub <= kPrSubs; ++sub) {
-      const bool cur = sub < kPrSubs;  // compile-time after unrolling
-      const bool prev = sub > 0;
-      f32x4 acc[RT];
-      float an = 0.0f;
-      if (cur) {
-        const u32x4 op = bq[sub & 1];
-        if (sub + 2 < kPrSubs) bq[sub & 1] = lds_operand<1>(buf, sub + 2, 0, m16, g);
-        an = athp_buf[sub * kColTile + m16];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma_step<kModeF16>(a[rt][0], op, nqp[rt]);
-      }
-      if (prev) {
-        float mx = -__builtin_inff();
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) mx = __builtin_fmaxf(mx, pacc[rt][i]);
-        }
-        pass |= __ballot(mx >= anp) != 0ull ? 1ull << (sub - 1) : 0ull;
-      }
-      if (cur) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) pacc[rt] = acc[rt];
-        anp = an;
-      }
-    }
-  } else {
-    const int64_t left = e_end - t0;
-    const int nsub = static_cast<int>((left + kColTile - 1) / kColTile);
+// Pairs that pass in the surviving column tiles `pass` of the LDS tile (all
+// lanes); a wave with more than half of its column tiles surviving is not
+// counted out.
+__device__ __forceinline__ int prefix_count(const unsigned char* buf, const float* athp_buf, uint32_t pass,
+                                            const u32x4 (&a)[kPrRT], const f32x16 (&nq)[kPrRT]) {
+  if (__builtin_popcount(pass) > kPrSubs / 2) return 1 << 20;
+  const int lane = lane_id();
+  int n = 0;
 #pragma unroll 1
-    for (int sub = 0; sub < nsub; ++sub) {
-      const u32x4 op = lds_operand<1>(buf, sub, 0, m16, g);
-      const float an = sub * kColTile + m16 < left ? athp_buf[sub * kColTile + m16] : __builtin_inff();
-      float mx = -__builtin_inff();
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const f32x4 acc = mfma_step<kModeF16>(a[rt][0], op, nqp[rt]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) mx = __builtin_fmaxf(mx, acc[i]);
-      }
-      pass |= __ballot(mx >= an) != 0ull ? 1ull << sub : 0ull;
-    }
+  for (uint32_t m = pass; m != 0u; m &= m - 1u) {
+    const int sub = __builtin_ctz(m);
+    n += __builtin_popcount(prefix_mask(*reinterpret_cast<const u32x4*>(buf + sub * (kPrCol * 32) + lane * 16),
+                                        athp_buf[sub * kPrCol + (lane & 31)], a, nq));
   }
-  if (__builtin_expect(pass != 0ull, 0)) {
-#pragma unroll 1
-    for (int sub = 0; sub < kPrSubs; ++sub)
-      if ((pass >> sub) & 1ull) prune_survivor<STORE, KS, RT>(p, t0, sub, e_end, qwave, qend, m16, g, a, rq);
-  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, kWave);
+  return n;
 }
 
-// The pruned scan (slice mode): one 512-thread workgroup per (query block,
-// cache slice), 8 waves of RT row tiles of queries, the query operands of
-// all KS k-steps in registers (the survivors need them), the negated prefix
-// thresholds of the lane's 16 queries as the start value of k-step 0.
-template <int STORE, int KS, int RT>
-__global__ __launch_bounds__(kDmaWaves * kWave, 2) void lookup_prune_kernel(const LookupParams p) {
-  static_assert(KS >= 2, "a prefix shorter than the row");
-  __shared__ __attribute__((aligned(16))) unsigned char buf0[kPrRows * 64];
-  __shared__ __attribute__((aligned(16))) unsigned char buf1[kPrRows * 64];
-  __shared__ __attribute__((aligned(16))) float athp0[kPrRows];
-  __shared__ __attribute__((aligned(16))) float athp1[kPrRows];
+// The workgroup's pairs on their way to the global queue: one reservation
+// there per slice instead of one per wave and pass (thousands of atomics on
+// one address held the waves up: 73 -> 37 us at B = 8,192, n = 65,536, d = 128).
+constexpr int kPrQueue = 512;
+struct PrefixQueue {
+  int32_t q[kPrQueue];  // query, relative to the workgroup's first
+  int32_t n;            // pairs offered (those past kPrQueue went straight to the global queue)
+  int64_t e[kPrQueue];  // cache row
+  int64_t base;
+};
+
+// A surviving column tile, rows [ebase, ebase + 32): its pairs found again
+// (the LDS tile may be gone) and queued.
+template <int STORE>
+__device__ __forceinline__ void prefix_survivor(const LookupParams& p, int64_t ebase, int64_t q0, int64_t qwave,
+                                                const u32x4 (&a)[kPrRT], const f32x16 (&nq)[kPrRT], PrefixQueue& pq) {
+  const int lane = lane_id();
+  const int64_t e = ebase + (lane & 31);
+  const u32x4 b = load_chunk<kModeF16, LIPCACHE_F16>(p.cimg, e < p.n ? e : p.n - 1, p.d, (lane >> 5) * 8);
+  uint32_t mask = prefix_mask(b, p.athr_p[e], a, nq);
+  if (mask != 0u) {
+    int slot = atomicAdd(&pq.n, __builtin_popcount(mask));
+    for (; mask != 0u && slot < kPrQueue; mask &= mask - 1u, ++slot) {
+      pq.q[slot] = static_cast<int32_t>(qwave - q0) + mask_row<32>(__builtin_ctz(mask), lane);
+      pq.e[slot] = e;
+    }
+  }
+  if (__ballot(mask != 0u) != 0ull) enqueue_pairs<STORE, 32>(p, mask, qwave, ebase, p.B, nullptr);
+}
+
+// The workgroup's queue to the global one (all waves; the queue is complete).
+template <int STORE>
+__device__ __forceinline__ void prefix_flush(const LookupParams& p, int64_t q0, PrefixQueue& pq) {
+  const int n = pq.n < kPrQueue ? pq.n : kPrQueue;
+  if (n == 0) return;
+  if (threadIdx.x == 0) pq.base = static_cast<int64_t>(atomicAdd(p.gq_count, static_cast<unsigned long long>(n)));
+  __syncthreads();
+  const int64_t base = pq.base;
+  const int64_t left = p.gq_cap - base;
+  const int room = left <= 0 ? 0 : left < n ? static_cast<int>(left) : n;
+  const int i = static_cast<int>(threadIdx.x);
+  if (i < room) {
+    p.gq_pos[base + i] = q0 + pq.q[i];
+    p.gq_e[base + i] = pq.e[i];
+  }
+  // no room in the global queue: settled here
+  if (room < n && threadIdx.x < kWave)
+    settle_queue<STORE>(recheck_args(p, p.B, nullptr), pq.q + room, pq.e + room, n - room, q0);
+}
+static_assert(kPrQueue <= kPrThreads, "one pair per thread");
+
+// Column tiles ew, ew + EW, ... of one prefix tile against the wave's 64
+// queries; returns the wave-uniform mask of those where a pair passes.
+template <int EW>
+__device__ __forceinline__ uint32_t prefix_tile(const unsigned char* buf, const float* athp_buf, int ew,
+                                                const u32x4 (&a)[kPrRT], const f32x16 (&nq)[kPrRT]) {
+  const int lane = lane_id();
+  const unsigned char* op = buf + ew * (kPrCol * 32) + lane * 16;
+  const float* at = athp_buf + ew * kPrCol + (lane & 31);
+  constexpr int kN = kPrSubs / EW;
+  uint32_t pass = 0u;
+  // -inf the compiler cannot see through: every maximum is one v_max3 (with
+  // the constant, or starting from two accumulators, it adds two v_max that
+  // only quieten NaNs)
+  float lowest = -__builtin_inff();
+  asm volatile("" : "+v"(lowest));
+  lowest = __builtin_canonicalizef(lowest);
+  u32x4 bn = *reinterpret_cast<const u32x4*>(op);
+  float ann = at[0];
+#pragma unroll 4
+  for (int s = 0; s < kN; ++s) {
+    // the next column tile's operand and threshold are read a tile ahead
+    // (past the last: the first again); the barrier keeps them there
+    const u32x4 b = bn;
+    const float an = ann;
+    const int nx = s + 1 < kN ? s + 1 : 0;
+    bn = *reinterpret_cast<const u32x4*>(op + nx * (EW * kPrCol * 32));
+    ann = at[nx * (EW * kPrCol)];
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16 acc[kPrRT];
+#pragma unroll
+    for (int rt = 0; rt < kPrRT; ++rt) acc[rt] = mfma_prefix(a[rt], b, nq[rt]);
+    float mx = lowest;
+#pragma unroll
+    for (int i = 0; i < 16 * kPrRT; ++i) mx = __builtin_fmaxf(mx, acc[i / 16][i % 16]);
+    pass |= __ballot(mx >= an) != 0ull ? 1u << (s * EW) : 0u;
+  }
+  return pass << ew;
+}
+
+template <int STORE, int EW>
+__global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const LookupParams p) {
+  // the thresholds first: their reads then fit the LDS instruction's offset
+  struct Tiles {
+    float athp[2][kPrRows];
+    unsigned char buf[2][kPrRows * 32];
+    int passed[2];  // pairs that passed, even and odd prefix tiles, running totals
+    PrefixQueue pq;
+  };
+  __shared__ __attribute__((aligned(16))) Tiles sh;
+  auto& athp = sh.athp;
+  auto& buf = sh.buf;
+  auto& passed = sh.passed;
+  constexpr int kQW = kPrWaves / EW;
+  constexpr int kLimit = kQW * 32;  // pairs that may pass per prefix tile
 
   int64_t q0, qend, e_begin, e_end;
-  block_work(p, kDmaWaves * RT * 16, q0, qend, e_begin, e_end);
-  qend = p.B;
+  block_work(p, kQW * kPrWaveQ, q0, qend, e_begin, e_end);
+  if (e_begin >= e_end) return;  // whole workgroup: an empty slice
   const int lane = lane_id();
   const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
-  const int m16 = lane & 15;
-  const int g = lane >> 4;
-  const int64_t qwave = q0 + wave * (RT * 16);
-  if (e_begin >= e_end) return;  // whole workgroup: an empty slice
-  issue_prefix_tile(buf0, athp0, p, e_begin, e_end, wave);
+  const int ew = wave / kQW;
+  const int64_t qwave = q0 + (wave % kQW) * kPrWaveQ;
+  const bool active = qwave < p.B;  // else only copies
+  if (threadIdx.x < 2) passed[threadIdx.x] = 0;
+  if (threadIdx.x == 2) sh.pq.n = 0;
+  issue_prefix_tile(buf[0], athp[0], p, e_begin, wave);
 
-  u32x4 a[RT][KS];
-  load_query_operands<kModeF16, KS, RT, false>(p, nullptr, qwave, qend, m16, g, a);
-  f32x4 nqp[RT];
-  load_thresholds<RT>(p.qthr_p, qwave, qend, nullptr, g, true, nqp);
-  RecheckQueue rq{nullptr, nullptr, 0};
-
-  for (int64_t t0 = e_begin;; t0 += 2 * kPrRows) {
-    wait_copies();
-    __syncthreads();
-    const bool more1 = t0 + kPrRows < e_end;
-    if (more1) issue_prefix_tile(buf1, athp1, p, t0 + kPrRows, e_end, wave);
-    prune_tile<STORE, KS, RT>(buf0, athp0, p, t0, e_end, qwave, qend, m16, g, a, nqp, rq);
-    if (!more1) break;
-    wait_copies();
-    __syncthreads();
-    const bool more2 = t0 + 2 * kPrRows < e_end;
-    if (more2) issue_prefix_tile(buf0, athp0, p, t0 + 2 * kPrRows, e_end, wave);
-    prune_tile<STORE, KS, RT>(buf1, athp1, p, t0 + kPrRows, e_end, qwave, qend, m16, g, a, nqp, rq);
-    if (!more2) break;
+  u32x4 a[kPrRT];
+  f32x16 nq[kPrRT];
+#pragma unroll
+  for (int rt = 0; rt < kPrRT; ++rt) {
+    const int64_t q = qwave + rt * 32 + (lane & 31);
+    a[rt] = load_chunk<kModeF16, LIPCACHE_F32>(p.zq, q < p.B ? q : p.B - 1, p.d, (lane >> 5) * 8);
+    // four consecutive queries per group (the array is padded to 64)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t qi = qwave + mask_row<32>(rt * 16 + 4 * j, lane);
+      f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (active) t = *reinterpret_cast<const f32x4*>(p.qthr_p + qi);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) nq[rt][4 * j + i] = qi + i < p.B ? -t[i] : -__builtin_inff();
+    }
   }
+
+  int seen[2] = {0, 0};
+  int total = 0, allowed = kLimit;
+  bool stopped = false;
+  uint32_t pass = 0u;
+  int64_t t0 = e_begin;
+  for (int cur = 0;; cur ^= 1, t0 += kPrRows) {
+    wait_copies();
+    __syncthreads();  // publishes tile t0 and the count of the tile before
+    if (t0 > e_begin) {
+      // Each slot only grows and is next added to after the following
+      // barrier, so every wave reads the same count and takes the same turn.
+      const int now = uniform(passed[cur ^ 1]);
+      total += now - seen[cur ^ 1];
+      seen[cur ^ 1] = now;
+      allowed += kLimit;
+      if (total > allowed) {
+        stopped = true;
+        break;
+      }
+    }
+    const bool more = t0 + kPrRows < e_end;
+    if (more) issue_prefix_tile(buf[cur ^ 1], athp[cur ^ 1], p, t0 + kPrRows, wave);
+    // settle the tile before while this tile's operands are in LDS
+    for (uint32_t m = pass; m != 0u; m &= m - 1u)
+      prefix_survivor<STORE>(p, t0 - kPrRows + __builtin_ctz(m) * kPrCol, q0, qwave, a, nq, sh.pq);
+    if (t0 >= e_end) break;
+    pass = active ? prefix_tile<EW>(buf[cur], athp[cur], ew, a, nq) : 0u;
+    if (pass != 0u) {
+      const int n = prefix_count(buf[cur], athp[cur], pass, a, nq);
+      if (lane == 0) atomicAdd(&passed[cur], n);
+    }
+  }
+  __syncthreads();  // the queue is complete
+  prefix_flush<STORE>(p, q0, sh.pq);
+  // The tile before t0 and the rest of the slice go to the full contraction.
+  if (stopped && threadIdx.x == 0) {
+    const int xcd = static_cast<int>(blockIdx.x) % kXcds;
+    const int64_t slot = static_cast<int64_t>(atomicAdd(&p.dn_count[xcd], 1ull)) + xcd * p.dn_cap;
+    p.dn_work[slot] = q0 * (1ll << 24) + e_begin / p.slice_len;
+    p.dn_row[slot] = t0 - kPrRows;
+  }
+}
+
+// The queue of a prefix scan: the full filter first (float16, all d features,
+// the full kernel's own instructions in its order, so its own dot products),
+// then the exact re-check of the pairs it passes.  A wave takes 16 pairs:
+// pair i is row i and column i of one 16x16 block, its dot product the
+// block's diagonal.  The filter reads half the bytes of the float64 sum and
+// drops most pairs the 16 features could not (and the counter keeps its
+// meaning: pairs both filters let through).  FOLD as kFoldQ.
+template <int SRC, bool FOLD>
+__global__ __launch_bounds__(256) void recheck_prefix_kernel(const RecheckArgs p, const void* __restrict__ cimg,
+                                                             const float* __restrict__ qthr,
+                                                             const float* __restrict__ athr,
+                                                             const int64_t* __restrict__ gpos,
+                                                             const int64_t* __restrict__ ge,
+                                                             const unsigned long long* __restrict__ gcount,
+                                                             int64_t cap) {
+  __shared__ unsigned int block_done;
+  const int lane = lane_id();
+  const int m16 = lane & 15, g = lane >> 4;
+  if (threadIdx.x == 0) block_done = 0u;
+  __syncthreads();
+  const int64_t reserved = static_cast<int64_t>(*gcount);
+  const int64_t total = reserved < cap ? reserved : cap;
+  const int64_t waves = static_cast<int64_t>(gridDim.x) * (blockDim.x / kWave);
+  const int64_t w = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
+  int done = 0;
+  for (int64_t b = w * 16; b < total; b += waves * 16) {
+    // pair b + m16, the last pair again past the end
+    const int64_t i = b + m16 < total ? b + m16 : total - 1;
+    const int64_t q = gpos[i], e = ge[i];
+    const float qq = qthr[q], an = athr[e];
+    f32x4 qrow;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) qrow[r] = __shfl(qq, 4 * g + r, kWave);
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = -qrow[r];
+    }
+#pragma unroll 4
+    for (int k0 = g * 8; k0 < p.d; k0 += 32)
+      acc = mfma_step<kModeF16>(load_chunk<kModeF16, LIPCACHE_F32>(p.zq, q, p.d, k0),
+                                load_chunk<kModeF16, LIPCACHE_F16>(cimg, e, p.d, k0), acc);
+    // lane (m16, g = m16 / 4) holds the diagonal element of pair m16
+    float v = acc[0];
+#pragma unroll
+    for (int r = 1; r < 4; ++r) v = (m16 & 3) == r ? acc[r] : v;
+    const bool pass = (FOLD ? v : v - qq) >= an;
+    unsigned long long keep = __ballot(pass && g == (m16 >> 2) && b + m16 < total);
+    while (keep != 0ull) {
+      // the next four: lane j < 4 takes the j-th set lane's pair
+      int src = 0;
+      bool mine = false;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (keep != 0ull) {
+          const int l = __builtin_ctzll(keep);
+          keep &= keep - 1ull;
+          if (lane == j) {
+            src = l;
+            mine = true;
+          }
+        }
+      }
+      const int64_t qs = __shfl(q, src, kWave), es = __shfl(e, src, kWave);
+      done += settle_four<SRC>(p, mine, mine ? qs : 0, mine ? es : 0);
+    }
+  }
+  if (lane == 0 && done) atomicAdd(&block_done, static_cast<unsigned int>(done));
+  __syncthreads();
+  if (threadIdx.x == 0 && block_done)
+    atomicAdd(&p.stats[LIPCACHE_STAT_RECHECKED], static_cast<unsigned long long>(block_done));
 }
 
 // ------------------------------------------------------------- dispatch
@@ -1520,24 +1737,24 @@ inline bool make_plan(int precision, const lipcache_cache* c, bool list, Plan& p
   return true;
 }
 
-// Kernel variants: the lookup, the filter dump, and the work-list lookup of
-// the cluster index.
-enum { kVarLookup = 0, kVarDump = 1, kVarList = 2, kVarList8 = 3 };
+// Kernel variants: the lookup, the filter dump, the work-list lookup of the
+// cluster index, and the slices a prefix scan listed.
+enum { kVarLookup = 0, kVarDump = 1, kVarList = 2, kVarList8 = 3, kVarDense = 4 };
 
 template <int MODE, int SRC, int KS, int VAR>
 hipError_t launch_v1(const LookupParams& p, unsigned grid, hipStream_t s) {
   hipLaunchKernelGGL((lookup_kernel<MODE, SRC, KS, (KS <= 8 ? 4 : (KS == 16 ? 2 : 1)), VAR == kVarDump,
-                                    VAR == kVarList || VAR == kVarList8>),
+                                    VAR == kVarList || VAR == kVarList8, VAR == kVarDense>),
                      dim3(grid), dim3(kLkThreads), 0, s, p);
   return hipGetLastError();
 }
 
 template <int MODE, int STORE, int KS, int VAR>
 hipError_t launch_dma(const LookupParams& p, unsigned grid, hipStream_t s) {
-  if constexpr (KS <= 16) {
+  if constexpr (KS <= 16 && !(VAR == kVarDense && KS < 2)) {
     constexpr int kNW = VAR == kVarList ? kListWaves : kDmaWaves;
     hipLaunchKernelGGL((lookup_dma_kernel<MODE, STORE, KS, (KS <= 8 ? 4 : 2), kNW, VAR == kVarDump,
-                                          VAR == kVarList || VAR == kVarList8>),
+                                          VAR == kVarList || VAR == kVarList8, VAR == kVarDense>),
                        dim3(grid), dim3(kNW * kWave), 0, s, p);
     return hipGetLastError();
   } else {
@@ -1572,27 +1789,50 @@ hipError_t launch_lookup(int precision, int store, const Plan& pl, const LookupP
                                : launch_ks<kModeF32, LIPCACHE_BF16, VAR>(pl, p, grid, s);
 }
 
-// The pruned scan (float16 image, 2 <= KS <= 16; see prune_consts).
+// The prefix scan, EW waves of a workgroup on the same 64 queries (prefix_ew).
 template <int STORE>
-hipError_t launch_prune_store(const Plan& pl, const LookupParams& p, unsigned grid, hipStream_t s) {
-  switch (pl.ks) {
-#define LC_PCASE(K)                                                                                            \
-  case K:                                                                                                      \
-    hipLaunchKernelGGL((lookup_prune_kernel<STORE, K, (K <= 8 ? 4 : 2)>), dim3(grid), dim3(kDmaWaves * kWave), 0, \
-                       s, p);                                                                                  \
+hipError_t launch_prefix_store(int ew, const LookupParams& p, unsigned grid, hipStream_t s) {
+  switch (ew) {
+#define LC_PCASE(E)                                                                                         \
+  case E:                                                                                                   \
+    hipLaunchKernelGGL((lookup_prefix_kernel<STORE, E>), dim3(grid), dim3(kPrThreads), 0, s, p);            \
     return hipGetLastError();
+    LC_PCASE(1)
     LC_PCASE(2)
     LC_PCASE(4)
     LC_PCASE(8)
-    LC_PCASE(16)
 #undef LC_PCASE
     default: return hipErrorInvalidValue;
   }
 }
 
-inline hipError_t launch_prune(int store, const Plan& pl, const LookupParams& p, unsigned grid, hipStream_t s) {
-  return store == LIPCACHE_F32 ? launch_prune_store<LIPCACHE_F32>(pl, p, grid, s)
-                               : launch_prune_store<LIPCACHE_BF16>(pl, p, grid, s);
+inline hipError_t launch_prefix(int store, int ew, const LookupParams& p, unsigned grid, hipStream_t s) {
+  return store == LIPCACHE_F32 ? launch_prefix_store<LIPCACHE_F32>(ew, p, grid, s)
+                               : launch_prefix_store<LIPCACHE_BF16>(ew, p, grid, s);
+}
+
+template <int STORE>
+hipError_t launch_prefix_recheck(int ks, unsigned grid, hipStream_t s, const RecheckArgs& ra, const void* cimg,
+                                 const float* qthr, const float* athr, const int64_t* gpos, const int64_t* ge,
+                                 const unsigned long long* gcount, int64_t cap) {
+  if (ks <= 4) {
+    static_assert(kFoldQ<kModeF16, 4> && !kFoldQ<kModeF16, 8>, "the full kernel's filter by width");
+    hipLaunchKernelGGL((recheck_prefix_kernel<STORE, true>), dim3(grid), dim3(256), 0, s, ra, cimg, qthr, athr, gpos,
+                       ge, gcount, cap);
+  } else {
+    hipLaunchKernelGGL((recheck_prefix_kernel<STORE, false>), dim3(grid), dim3(256), 0, s, ra, cimg, qthr, athr, gpos,
+                       ge, gcount, cap);
+  }
+  return hipGetLastError();
+}
+
+// Waves that share 64 queries: the fewest query blocks the batch fills.
+inline int prefix_ew(int64_t B) { return B <= kPrWaveQ ? 8 : B <= 2 * kPrWaveQ ? 4 : B <= 4 * kPrWaveQ ? 2 : 1; }
+
+inline hipError_t launch_dense(int store, const Plan& pl, const LookupParams& p, hipStream_t s) {
+  const unsigned grid = 256;  // one workgroup per CU, all of them drain the lists
+  return store == LIPCACHE_F32 ? launch_ks<kModeF16, LIPCACHE_F32, kVarDense>(pl, p, grid, s)
+                               : launch_ks<kModeF16, LIPCACHE_BF16, kVarDense>(pl, p, grid, s);
 }
 
 // Workgroups a slice scan aims for (at least a few per CU, for balance).
@@ -1600,6 +1840,9 @@ inline hipError_t launch_prune(int store, const Plan& pl, const LookupParams& p,
 #define LC_GRID_TARGET 256
 #endif
 constexpr int64_t kGridTarget = LC_GRID_TARGET;
+
+// Workgroups of the prefix scan the chip holds at once (two per CU).
+constexpr int64_t kPrGridTurn = 512;
 
 // The global re-check queue of a scan (workspace memory): 4 B + 65536
 // pairs; a pair that finds it full is re-checked by its wave at once.
@@ -1619,7 +1862,7 @@ struct Workspace {
   unsigned long long* stats;
   float* athr;
   GlobalRecheckWs gq;
-  float* qthr_p;  // pruned lookup only: Q'_q [B], A'_i [athp_len(N)]
+  float* qthr_p;  // prefix scan only: Q'_q [B], A'_i [athp_len(N)]
   float* athr_p;
 };
 
@@ -1629,7 +1872,7 @@ inline int64_t athr_len(int64_t n) {
   return ((n > 0 ? n : 0) + kDmaMaxRows - 1) / kDmaMaxRows * kDmaMaxRows + kDmaMaxRows;
 }
 
-// A'_i of the pruned scan, padded with +inf so that a prefix tile starting
+// A'_i of the prefix scan, padded with +inf so that a prefix tile starting
 // below n reads only this array.
 inline int64_t athp_len(int64_t n) { return ((n > 0 ? n : 0) + kPrRows - 1) / kPrRows * kPrRows + kPrRows; }
 
@@ -1691,8 +1934,9 @@ struct FilterConsts {
   Plan pl_list;    // work-list scan: 4-wave blocks (short cluster lists)
   Plan pl_list8;   // work-list scan: 8-wave blocks (long cluster lists)
   Thresholds t;
-  bool prune = false;  // pruned slice scan (prefix thresholds tp)
+  bool prune = false;  // prefix scan (thresholds tp, image norm bounds pn)
   Thresholds tp;
+  PrefixNorm pn;
 };
 
 // Precision argument: the filter precision, optionally | LIPCACHE_LOOKUP_PRUNE.
@@ -1714,14 +1958,25 @@ lipcache_status lookup_consts(const lipcache_cache* c, int32_t precision, Filter
   return LIPCACHE_OK;
 }
 
-// The pruned scan runs where the slice kernel is the float16 DMA kernel with
-// at least two k-steps, on caches of at least kPruneMinRows rows (fewer fill
-// too few 1024-row prefix tiles to pay for the prefix thresholds); elsewhere
-// the option changes nothing.
+// The prefix scan runs on the float16 image for rows of at least two k-steps,
+// on caches of at least kPruneMinRows rows (fewer fill too few 1024-row prefix
+// tiles to pay for the prefix thresholds).
 constexpr int64_t kPruneMinRows = 32 * kPrRows;
 
+// Whether a lookup that does not ask for the prefix scan takes it: the matrix
+// work it saves, (B rounded up to the full kernel's 512 queries) n (d - 32),
+// against the launch and the prefix thresholds it adds.  Measured over d =
+// 64 .. 512, n = 32K .. 262K, B = 1 .. 8,192 (full against prefix scan): even
+// at 2^33 (d = 64, n = 262,144, B = 1,024: 47.1 and 47.3 us; d = 256, n =
+// 65,536, B <= 512: 49 and 34-40 us), 5 us slower at a quarter of it (34.8
+// and 39.7 us, launches), 1.5x faster at four times it and 9x at the headline.
+inline bool prefix_pays(int64_t B, int64_t n, int d) {
+  const double b = static_cast<double>((B + 511) / 512 * 512);
+  return b * static_cast<double>(n) * static_cast<double>(d - kPrefixDims * 2) >= 8589934592.0;
+}
+
 void prune_consts(const lipcache_cache* c, int32_t precision, FilterConsts& fc) {
-  fc.prune = precision == LIPCACHE_F16 && fc.pl.dma && fc.pl.ks >= 2 && fc.pl.ks <= 16 && c->n >= kPruneMinRows;
+  fc.prune = precision == LIPCACHE_F16 && c->zimg != nullptr && fc.pl.ks >= 2 && c->n >= kPruneMinRows;
   if (!fc.prune) return;
   const FilterSlack fs = filter_slack(precision, c->store_dtype, kPrefixDims);
   const double u32 = 1.0 / 16777216.0;
@@ -1736,6 +1991,9 @@ void prune_consts(const lipcache_cache* c, int32_t precision, FilterConsts& fc) 
   fc.tp.eta1 = fs.eta1 * (1.0 + 2.0 * gam);
   fc.tp.eta0 = fs.eta0 * (1.0 + 2.0 * gam);
   fc.tp.range2 = fs.range2;
+  const double u = c->store_dtype == LIPCACHE_BF16 ? 0.0 : 1.0 / 2048.0;
+  fc.pn.lo = (1.0 - 1e-15) / (1.0 + u);
+  fc.pn.hi = (1.0 + 1e-15) / (1.0 - u);
 }
 
 // Stage 1: Q_q, and the reset of best / band flags / counters; with `view`
@@ -1748,13 +2006,14 @@ lipcache_status lookup_stage_prep(const float* zq, int64_t B, int d, const Filte
                                   unsigned long long* gq_count = nullptr, double* qnorm = nullptr,
                                   uint16_t* zq16 = nullptr, float* qthr_p = nullptr, float* athr_p = nullptr) {
   const int64_t qblocks = B > 0 ? (B + kLkWaves - 1) / kLkWaves : 1;
-  PrepEntries pe{nullptr, nullptr, 0, 0, nullptr, nullptr, qnorm, zq16, nullptr, nullptr, 0, nullptr, 0, fc.tp};
+  PrepEntries pe{nullptr, nullptr, 0, 0, nullptr, nullptr, qnorm, zq16, nullptr, nullptr, 0, nullptr, fc.tp, fc.pn,
+                 nullptr};
   int64_t eblocks = 0;
   if (view && view->n > 0) {
     const bool pr = qthr_p && athr_p;
     pe = PrepEntries{view->r, view->norm2, view->n, athr_len(view->n), athr, gq_count, qnorm, zq16,
-                     pr ? qthr_p : nullptr, pr ? athr_p : nullptr, pr ? athp_len(view->n) : 0, view->z,
-                     view->store_dtype, fc.tp};
+                     pr ? qthr_p : nullptr, pr ? athr_p : nullptr, pr ? athp_len(view->n) : 0, view->zimg,
+                     fc.tp, fc.pn, pr ? gq_count + 1 : nullptr};
     const int64_t cover = pe.np_pad > pe.n_pad ? pe.np_pad : pe.n_pad;
     eblocks = (cover + kLkThreads - 1) / kLkThreads;
   }
@@ -1817,14 +2076,43 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
   p.gq_pos = dump ? nullptr : gq.pos;
   p.gq_e = dump ? nullptr : gq.e;
   p.gq_count = dump ? nullptr : gq.count;
-  p.gq_cap = dump ? 0 : gq.cap;
+  int64_t gq_cap = dump ? 0 : gq.cap;
+  p.dn_work = nullptr;
+  p.dn_row = nullptr;
+  p.dn_count = nullptr;
+  p.dn_cap = 0;
+  p.pf_qblock = 0;
   int64_t grid = n_items;
   p.slice_len = 0;
   const bool prune = qthr_p && athr_p && !items && !dump;
-  if (!items) {
+  const int ew = prefix_ew(B);
+  if (prune) {
+    // Slices of whole prefix tiles, a multiple of 8 (one set per XCD): four
+    // turns of the chip (two workgroups per CU) while a slice keeps four
+    // tiles, and one turn while it keeps one.
+    p.pf_qblock = kPrWaves / ew * kPrWaveQ;
+    p.n_qblocks = static_cast<int>((B + p.pf_qblock - 1) / p.pf_qblock);
+    const int64_t tiles = (view->n + kPrRows - 1) / kPrRows;
+    const int64_t per8 = kXcds * static_cast<int64_t>(p.n_qblocks);
+    const int64_t want4 = (4 * kPrGridTurn + per8 - 1) / per8, want1 = (kPrGridTurn + per8 - 1) / per8;
+    const int64_t most4 = tiles / (kXcds * 4), most1 = (tiles + kXcds - 1) / kXcds;
+    int64_t s8 = want4 < most4 ? want4 : most4;
+    const int64_t one = want1 < most1 ? want1 : most1;
+    if (s8 < one) s8 = one;
+    if (s8 < 1) s8 = 1;
+    const int64_t slices = kXcds * s8;
+    p.slice_len = ((tiles + slices - 1) / slices) * kPrRows;
+    grid = slices * p.n_qblocks;
+    // the lists of slices for the full kernel take the queue's last slots
+    p.dn_cap = s8 * p.n_qblocks;
+    gq_cap -= grid;
+    p.dn_work = gq.pos + gq_cap;
+    p.dn_row = gq.e + gq_cap;
+    p.dn_count = gq.count + 1;
+  } else if (!items) {
     // Cache slices: a multiple of 8 (one set per XCD), enough blocks to fill
     // the chip (~kGridTarget), but at least 4 tiles per slice.
-    const int64_t tile_rows = prune ? kPrRows : pl.tile_rows;
+    const int64_t tile_rows = pl.tile_rows;
     const int64_t tiles = (view->n + tile_rows - 1) / tile_rows;
     int64_t s8 = (kGridTarget + kXcds * p.n_qblocks - 1) / (kXcds * static_cast<int64_t>(p.n_qblocks));
     int64_t s8_max = tiles / (kXcds * 4);
@@ -1835,26 +2123,38 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
     p.slice_len = ((tiles + slices - 1) / slices) * tile_rows;
     grid = slices * p.n_qblocks;
   }
-  if (grid > INT_MAX) return LIPCACHE_EUNSUPPORTED;
+  if (grid > INT_MAX || gq_cap < 0) return LIPCACHE_EUNSUPPORTED;
+  p.gq_cap = gq_cap;
+  p.near_only = prune;
   const unsigned gu = static_cast<unsigned>(grid);
   const hipError_t e = dump    ? launch_lookup<kVarDump>(precision, view->store_dtype, pl, p, gu, s)
                        : items ? (pl.waves == kListWaves ? launch_lookup<kVarList>(precision, view->store_dtype, pl, p, gu, s)
                                                          : launch_lookup<kVarList8>(precision, view->store_dtype, pl, p, gu, s))
-                       : prune ? launch_prune(view->store_dtype, pl, p, gu, s)
+                       : prune ? launch_prefix(view->store_dtype, ew, p, gu, s)
                                : launch_lookup<kVarLookup>(precision, view->store_dtype, pl, p, gu, s);
   if (e != hipSuccess) return LIPCACHE_EHIP;
+  if (prune && launch_dense(view->store_dtype, pl, p, s) != hipSuccess) return LIPCACHE_EHIP;
   if (dump) return LIPCACHE_OK;
   // the pairs the scan's waves queued, one chip-wide pass
   const RecheckArgs ra{zq, view->z, view->r, best, bflag, stats, static_cast<int64_t>(LLONG_MAX), view->n, view->d,
-                       emap, eoff, qlist};
-  int64_t blocks = (gq.cap + 15) / 16;
+                       emap, eoff, qlist, false};
+  int64_t blocks = (gq_cap + 15) / 16;
   if (blocks > 512) blocks = 512;
+  if (prune) {
+    const hipError_t er =
+        view->store_dtype == LIPCACHE_BF16
+            ? launch_prefix_recheck<LIPCACHE_BF16>(pl.ks, static_cast<unsigned>(blocks), s, ra, p.cimg, qthr, athr,
+                                                   gq.pos, gq.e, gq.count, gq_cap)
+            : launch_prefix_recheck<LIPCACHE_F32>(pl.ks, static_cast<unsigned>(blocks), s, ra, p.cimg, qthr, athr,
+                                                  gq.pos, gq.e, gq.count, gq_cap);
+    return er == hipSuccess ? LIPCACHE_OK : LIPCACHE_EHIP;
+  }
   if (view->store_dtype == LIPCACHE_BF16) {
     hipLaunchKernelGGL(recheck_queue_kernel<LIPCACHE_BF16>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, ra,
-                       gq.pos, gq.e, gq.count, gq.cap);
+                       gq.pos, gq.e, gq.count, gq_cap);
   } else {
     hipLaunchKernelGGL(recheck_queue_kernel<LIPCACHE_F32>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, ra,
-                       gq.pos, gq.e, gq.count, gq.cap);
+                       gq.pos, gq.e, gq.count, gq_cap);
   }
   LC_LAUNCHED();
   return LIPCACHE_OK;
@@ -1916,9 +2216,12 @@ lipcache_status run_lookup(const lipcache_cache* c, const float* zq, int64_t B, 
   FilterConsts fc;
   const lipcache_status cs = lookup_consts(c, precision, fc);
   if (cs != LIPCACHE_OK) return cs;
-  if (wants_prune(precision_arg)) prune_consts(c, precision, fc);
   const size_t need = ws_layout(B, c->n, nullptr, nullptr, wants_prune(precision_arg));
   if (!ws || ws_bytes < need || !aligned256(ws)) return LIPCACHE_EWORKSPACE;
+  // the prefix scan also without the option, where it pays and the workspace holds it
+  if (!dump && (wants_prune(precision_arg) || (prefix_pays(B, c->n, c->d) &&
+                                               ws_bytes >= ws_layout(B, c->n, nullptr, nullptr, true))))
+    prune_consts(c, precision, fc);
   return lookup_on(c, zq, B, precision, fc, label_out, index_out, dist2_out, stats, band_flag, ws, s, dump, g_hat,
                    cand);
 }
@@ -2065,7 +2368,7 @@ extern "C" int32_t lipcache_lookup_prunes(const lipcache_cache* c, int32_t preci
   FilterConsts fc;
   if (lookup_consts(c, precision, fc) != LIPCACHE_OK) return 0;
   prune_consts(c, precision, fc);
-  return fc.prune ? 1 : 0;
+  return fc.prune && fc.pl.ks <= 16 ? 1 : 0;
 }
 
 extern "C" size_t lipcache_lookup_workspace_bytes(int64_t B, int64_t N, int32_t d, int32_t precision) {
@@ -2098,8 +2401,10 @@ extern "C" lipcache_status lipcache_lookup_noalloc(const lipcache_cache* c, cons
   FilterConsts fc;
   const lipcache_status cs = lookup_consts(c, precision, fc);
   if (cs != LIPCACHE_OK) return cs;
-  if (wants_prune(precision_arg)) prune_consts(c, precision, fc);
   if (ws_layout(B, c->n, nullptr, nullptr, wants_prune(precision_arg)) > kNoAllocBytes) return LIPCACHE_EWORKSPACE;
+  if (wants_prune(precision_arg) ||
+      (prefix_pays(B, c->n, c->d) && ws_layout(B, c->n, nullptr, nullptr, true) <= kNoAllocBytes))
+    prune_consts(c, precision, fc);
   void* ws = device_scratch();
   if (!ws) return LIPCACHE_EHIP;
   return lookup_on(c, zq, B, precision, fc, label_out, index_out, dist2_out, stats, band_flag, ws,
