@@ -9,8 +9,10 @@
 // in float64; float32 accumulation would move a large share of the radii by
 // more than 1e-5 relative.
 //
-// Two kernels.  For d <= 512 the logits run on the float64 matrix cores
-// (certify_mfma_kernel, below).  For wider features a vector kernel is used:
+// Three kernels.  Larger batches (d <= 512, C > 32) go through a float16
+// filter that leaves only the classes that can matter to float64
+// (certify_filter.hip); the rows it cannot settle, and smaller batches, run
+// all logits on the float64 matrix cores (certify_mfma_kernel, below).  For wider features a vector kernel is used:
 // a workgroup of four waves owns a tile of E = 32 features, staged once in
 // LDS.  Lane e of every wave works on feature e; wave w runs over the class
 // chunks w, w+4, w+8, ... (eight classes per chunk), so the head row it
@@ -24,14 +26,13 @@
 // distances built once per call.
 #include <limits.h>
 
-#include "lc_common.hpp"
+#include "lc_certify.hpp"
 
 namespace lc {
 
 constexpr int kCertThreads = 256;
 constexpr int kCertWaves = kCertThreads / kWave;
 constexpr int kCertChunk = 8;
-constexpr double kSqrt2 = 1.4142135623730951;  // float64 nearest to sqrt(2)
 
 __global__ void widen_kernel(const float* __restrict__ src, int64_t n, double* __restrict__ dst) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -49,33 +50,54 @@ __device__ __forceinline__ void top2_push(double s, int c, double& v1, int& i1, 
 }
 
 // dist[y * C + j] = ||W_y - W_j||_2 in float64 (the denominator of the
-// per-pair radius of Remark 5.1).
-__global__ void row_distance_kernel(const double* __restrict__ W64, int C, int d, double* __restrict__ dist) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= static_cast<int64_t>(C) * C) return;
-  const int y = static_cast<int>(t / C);
-  const int j = static_cast<int>(t % C);
-  const double* a = W64 + static_cast<int64_t>(y) * d;
-  const double* b = W64 + static_cast<int64_t>(j) * d;
+// per-pair radius of Remark 5.1): 16x16 pairs per workgroup, both sets of rows
+// staged in LDS 64 features at a time (one thread per pair over global memory
+// took 41 us at C = 200, d = 256, the workgroup's rows from LDS 12 us).
+constexpr int kRdTile = 16;
+constexpr int kRdChunk = 64;
+
+__global__ __launch_bounds__(kRdTile * kRdTile) void row_distance_kernel(const float* __restrict__ W, int C, int d,
+                                                                        double* __restrict__ dist) {
+  __shared__ double wa[kRdTile][kRdChunk + 1], wb[kRdTile][kRdChunk + 1];
+  const int tx = static_cast<int>(threadIdx.x) % kRdTile, ty = static_cast<int>(threadIdx.x) / kRdTile;
+  const int y0 = static_cast<int>(blockIdx.y) * kRdTile, j0 = static_cast<int>(blockIdx.x) * kRdTile;
   double acc = 0.0;
-  for (int k = 0; k < d; ++k) {
-    const double diff = a[k] - b[k];
-    acc = __builtin_fma(diff, diff, acc);
+  for (int k0 = 0; k0 < d; k0 += kRdChunk) {
+    __syncthreads();
+    for (int t = static_cast<int>(threadIdx.x); t < kRdTile * kRdChunk; t += kRdTile * kRdTile) {
+      const int row = t / kRdChunk, k = t % kRdChunk;
+      const bool in = k0 + k < d;
+      wa[row][k] = in && y0 + row < C ? static_cast<double>(W[static_cast<int64_t>(y0 + row) * d + k0 + k]) : 0.0;
+      wb[row][k] = in && j0 + row < C ? static_cast<double>(W[static_cast<int64_t>(j0 + row) * d + k0 + k]) : 0.0;
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (int k = 0; k < kRdChunk; ++k) {
+      const double diff = wa[ty][k] - wb[tx][k];
+      acc = __builtin_fma(diff, diff, acc);
+    }
   }
-  dist[t] = __builtin_sqrt(acc);
+  if (y0 + ty < C && j0 + tx < C) dist[static_cast<int64_t>(y0 + ty) * C + j0 + tx] = __builtin_sqrt(acc);
 }
 
 // dmax[y] = max over j with dist[y * C + j] > 0 of that distance (0 when
-// every other row equals W_y): bounds every denominator of row y.
-__global__ void row_dmax_kernel(const double* __restrict__ dist, int C, double* __restrict__ dmax) {
-  const int y = static_cast<int>(blockIdx.x) * blockDim.x + threadIdx.x;
+// every other row equals W_y): bounds every denominator of row y.  One wave
+// per row (one thread per row took 24 us at C = 200, this 3 us).
+__global__ __launch_bounds__(kCertThreads) void row_dmax_kernel(const double* __restrict__ dist, int C,
+                                                               double* __restrict__ dmax) {
+  const int y = static_cast<int>(blockIdx.x) * kCertWaves + static_cast<int>(threadIdx.x) / kWave;
   if (y >= C) return;
   double m = 0.0;
-  for (int j = 0; j < C; ++j) {
+  for (int j = lane_id(); j < C; j += kWave) {
     const double v = dist[static_cast<int64_t>(y) * C + j];
     m = v > m ? v : m;
   }
-  dmax[y] = m;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const double v = __shfl_xor(m, o, kWave);
+    m = v > m ? v : m;
+  }
+  if (lane_id() == 0) dmax[y] = m;
 }
 
 // W z (no bias) for the classes c0 .. c0 + 7 below C, from the lane's feature
@@ -269,17 +291,6 @@ constexpr int kCmClasses = 32;     // head rows per LDS stage
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void top2_merge(double w1, int j1, double w2, double& v1, int& i1, double& v2) {
-  if (w1 > v1 || (w1 == v1 && j1 < i1)) {
-    v2 = v1 > v2 ? v1 : v2;
-    v1 = w1;
-    i1 = j1;
-  } else {
-    v2 = w1 > v2 ? w1 : v2;
-  }
-  v2 = w2 > v2 ? w2 : v2;
-}
-
 // Features past d are zero on both sides (registers and LDS), so every
 // k-group runs and adds exact zeros there.
 template <int KQ>
@@ -315,11 +326,13 @@ __device__ __forceinline__ void stage_head(const float* __restrict__ W, int C, i
   }
 }
 
+// With `pending` a fixed grid looks every block of rows through for labels the
+// filter left (kCertPending), and forms and writes only those.
 template <bool BF16_STORE, bool TIGHT, int KQ>
 __global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
     const float* __restrict__ z, int64_t N, int d, const float* __restrict__ W, const float* __restrict__ b, int C,
     double sigma, const double* __restrict__ row_dist, const double* __restrict__ dmax, int32_t* __restrict__ label_out,
-    float* __restrict__ r_out, float* __restrict__ margin_out, float* __restrict__ norm2_out) {
+    float* __restrict__ r_out, float* __restrict__ margin_out, float* __restrict__ norm2_out, bool pending) {
   extern __shared__ float wl[];  // kCmClasses rows of stride 16 KQ + 4 floats
   constexpr int kWidth = 16 * KQ;
   constexpr int stride = kWidth + 4;
@@ -327,7 +340,13 @@ __global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
   const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
   const int m16 = lane & 15, g = lane >> 4;
   const int nk = d / 16;
-  const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kCmRows + wave * 16;
+  const int64_t blocks = (N + kCmRows - 1) / kCmRows;
+  for (int64_t blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
+  const int64_t row0 = blk * kCmRows + wave * 16;
+  if (pending) {
+    const int64_t e = blk * kCmRows + lane;
+    if (!__syncthreads_or(wave == 0 && e < N && label_out[e] == kCertPending ? 1 : 0)) continue;
+  }
 
   // A operands: feature row0 + m16, k = 16 kq + 4 g + j (stored values)
   f32x4 za[KQ];
@@ -513,7 +532,7 @@ __global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
   const double n_out = __shfl(nrm, g + 4 * (m16 & 3), kWave);
   if (m16 < 4) {
     const int64_t i = row0 + g + 4 * m16;
-    if (i < N) {
+    if (i < N && (!pending || label_out[i] == kCertPending)) {
       double rv = r[0], mv = v1[0] - v2[0];
       int lab = i1[0];
 #pragma unroll
@@ -529,6 +548,7 @@ __global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
       if (margin_out) margin_out[i] = static_cast<float>(mv);
       if (norm2_out) norm2_out[i] = static_cast<float>(n_out);
     }
+  }
   }
 }
 
@@ -552,57 +572,58 @@ hipError_t launch_certify(unsigned grid, size_t lds, hipStream_t s, const float*
   return hipGetLastError();
 }
 
+// What a float64 launch over N rows takes (pending: see certify_mfma_kernel).
+struct MfmaArgs {
+  const float* z;
+  int64_t N;
+  int d;
+  const float* W;
+  const float* b;
+  int C;
+  double sigma;
+  const double* row_dist;
+  const double* dmax;
+  int32_t* label_out;
+  float* r_out;
+  float* margin_out;
+  float* norm2_out;
+  bool pending;
+};
+
 template <bool BF16_STORE, bool TIGHT, int KQ>
-hipError_t launch_mfma_kq(unsigned grid, size_t lds, hipStream_t s, const float* z, int64_t N, int d, const float* W,
-                          const float* b, int C, double sigma, const double* row_dist, const double* dmax, int32_t* label_out,
-                          float* r_out, float* margin_out, float* norm2_out) {
+hipError_t launch_mfma_kq(unsigned grid, hipStream_t s, const MfmaArgs& a) {
+  constexpr size_t lds = static_cast<size_t>(kCmClasses) * (16 * KQ + 4) * sizeof(float);
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(certify_mfma_kernel<BF16_STORE, TIGHT, KQ>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((certify_mfma_kernel<BF16_STORE, TIGHT, KQ>), dim3(grid), dim3(kCmThreads), lds, s, z, N, d, W,
-                     b, C, sigma, row_dist, dmax, label_out, r_out, margin_out, norm2_out);
+  hipLaunchKernelGGL((certify_mfma_kernel<BF16_STORE, TIGHT, KQ>), dim3(grid), dim3(kCmThreads), lds, s, a.z, a.N, a.d,
+                     a.W, a.b, a.C, a.sigma, a.row_dist, a.dmax, a.label_out, a.r_out, a.margin_out, a.norm2_out,
+                     a.pending);
   return hipGetLastError();
 }
 
 template <bool BF16_STORE, bool TIGHT>
-hipError_t launch_mfma_d(int d, unsigned grid, size_t lds, hipStream_t s, const float* z, int64_t N, const float* W,
-                         const float* b, int C, double sigma, const double* row_dist, const double* dmax, int32_t* label_out,
-                         float* r_out, float* margin_out, float* norm2_out) {
+hipError_t launch_mfma_d(unsigned grid, hipStream_t s, const MfmaArgs& a) {
   // registers for d / 16 k-groups, rounded up to a power of two
-  const int nk = d / 16;
-  if (nk <= 2)
-    return launch_mfma_kq<BF16_STORE, TIGHT, 2>(grid, lds, s, z, N, d, W, b, C, sigma, row_dist, dmax, label_out, r_out,
-                                                margin_out, norm2_out);
-  if (nk <= 4)
-    return launch_mfma_kq<BF16_STORE, TIGHT, 4>(grid, lds, s, z, N, d, W, b, C, sigma, row_dist, dmax, label_out, r_out,
-                                                margin_out, norm2_out);
-  if (nk <= 8)
-    return launch_mfma_kq<BF16_STORE, TIGHT, 8>(grid, lds, s, z, N, d, W, b, C, sigma, row_dist, dmax, label_out, r_out,
-                                                margin_out, norm2_out);
-  if (nk <= 16)
-    return launch_mfma_kq<BF16_STORE, TIGHT, 16>(grid, lds, s, z, N, d, W, b, C, sigma, row_dist, dmax, label_out, r_out,
-                                                 margin_out, norm2_out);
-  return launch_mfma_kq<BF16_STORE, TIGHT, 32>(grid, lds, s, z, N, d, W, b, C, sigma, row_dist, dmax, label_out, r_out,
-                                               margin_out, norm2_out);
+  const int nk = a.d / 16;
+  if (nk <= 2) return launch_mfma_kq<BF16_STORE, TIGHT, 2>(grid, s, a);
+  if (nk <= 4) return launch_mfma_kq<BF16_STORE, TIGHT, 4>(grid, s, a);
+  if (nk <= 8) return launch_mfma_kq<BF16_STORE, TIGHT, 8>(grid, s, a);
+  if (nk <= 16) return launch_mfma_kq<BF16_STORE, TIGHT, 16>(grid, s, a);
+  return launch_mfma_kq<BF16_STORE, TIGHT, 32>(grid, s, a);
 }
 
-hipError_t launch_certify_mfma(bool bf16, bool tight, int d, unsigned grid, size_t lds, hipStream_t s, const float* z,
-                               int64_t N, const float* W, const float* b, int C, double sigma,
-                               const double* row_dist, const double* dmax, int32_t* label_out, float* r_out, float* margin_out,
-                               float* norm2_out) {
-  if (bf16 && tight)
-    return launch_mfma_d<true, true>(d, grid, lds, s, z, N, W, b, C, sigma, row_dist, dmax, label_out, r_out, margin_out,
-                                     norm2_out);
-  if (bf16)
-    return launch_mfma_d<true, false>(d, grid, lds, s, z, N, W, b, C, sigma, row_dist, dmax, label_out, r_out, margin_out,
-                                      norm2_out);
-  if (tight)
-    return launch_mfma_d<false, true>(d, grid, lds, s, z, N, W, b, C, sigma, row_dist, dmax, label_out, r_out, margin_out,
-                                      norm2_out);
-  return launch_mfma_d<false, false>(d, grid, lds, s, z, N, W, b, C, sigma, row_dist, dmax, label_out, r_out, margin_out,
-                                     norm2_out);
+// Workgroups that look for the rows the filter left (the chip several times over).
+constexpr int64_t kCmPendingGrid = 2048;
+
+hipError_t launch_certify_mfma(bool bf16, bool tight, hipStream_t s, const MfmaArgs& a) {
+  int64_t blocks = (a.N + kCmRows - 1) / kCmRows;
+  if (a.pending && blocks > kCmPendingGrid) blocks = kCmPendingGrid;
+  const unsigned grid = static_cast<unsigned>(blocks);
+  if (bf16) return tight ? launch_mfma_d<true, true>(grid, s, a) : launch_mfma_d<true, false>(grid, s, a);
+  return tight ? launch_mfma_d<false, true>(grid, s, a) : launch_mfma_d<false, false>(grid, s, a);
 }
 
 }  // namespace
@@ -636,8 +657,8 @@ extern "C" lipcache_status lipcache_certify(const float* z, int64_t N, int32_t d
   double* W64 = static_cast<double*>(ws);
   const int64_t cd = static_cast<int64_t>(C) * d;
   const bool tight = radius_mode == LIPCACHE_RADIUS_TIGHT;
-  // the float64 copy of W feeds the row distances and the vector kernel
-  if (tight || d > 512) {
+  // the float64 copy of W feeds the vector kernel
+  if (d > 512) {
     hipLaunchKernelGGL(widen_kernel, dim3(static_cast<unsigned>((cd + 255) / 256)), dim3(256), 0, s, W, cd, W64);
     LC_LAUNCHED();
   }
@@ -647,24 +668,25 @@ extern "C" lipcache_status lipcache_certify(const float* z, int64_t N, int32_t d
     row_dist = reinterpret_cast<double*>(static_cast<unsigned char*>(ws) + head_bytes(C, d));
     dmax = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(row_dist) +
                                      align_up(static_cast<size_t>(C) * C * sizeof(double), 256));
-    const int64_t cc = static_cast<int64_t>(C) * C;
-    hipLaunchKernelGGL(row_distance_kernel, dim3(static_cast<unsigned>((cc + 255) / 256)), dim3(256), 0, s, W64, C, d,
-                       row_dist);
+    const unsigned rt = static_cast<unsigned>((C + kRdTile - 1) / kRdTile);
+    hipLaunchKernelGGL(row_distance_kernel, dim3(rt, rt), dim3(kRdTile * kRdTile), 0, s, W, C, d, row_dist);
     LC_LAUNCHED();
-    hipLaunchKernelGGL(row_dmax_kernel, dim3(static_cast<unsigned>((C + 255) / 256)), dim3(256), 0, s, row_dist, C,
-                       dmax);
+    hipLaunchKernelGGL(row_dmax_kernel, dim3(static_cast<unsigned>((C + kCertWaves - 1) / kCertWaves)),
+                       dim3(kCertThreads), 0, s, row_dist, C, dmax);
     LC_LAUNCHED();
   }
 
   if (d <= 512) {
-    int kq = 2;
-    while (16 * kq < d) kq *= 2;
-    const size_t lds_m = static_cast<size_t>(kCmClasses) * (16 * kq + 4) * sizeof(float);
-    const unsigned grid_m = static_cast<unsigned>((N + kCmRows - 1) / kCmRows);
-    const hipError_t em = launch_certify_mfma(store_dtype == LIPCACHE_BF16, radius_mode == LIPCACHE_RADIUS_TIGHT, d,
-                                              grid_m, lds_m, s, z, N, W, b, C, sigma, row_dist, dmax, label_out, r_out,
-                                              margin_out, norm2_out);
-    return em == hipSuccess ? LIPCACHE_OK : LIPCACHE_EHIP;
+    const bool bf16 = store_dtype == LIPCACHE_BF16;
+    MfmaArgs a{z, N, d, W, b, C, sigma, row_dist, dmax, label_out, r_out, margin_out, norm2_out, false};
+    if (certify_filter_takes(N, d, C)) {
+      // the head's image takes the place of the float64 copy
+      if (certify_filter_run(z, N, d, W, b, C, sigma, bf16, tight, row_dist, label_out, r_out, margin_out, norm2_out,
+                             ws, s) != hipSuccess)
+        return LIPCACHE_EHIP;
+      a.pending = true;
+    }
+    return launch_certify_mfma(bf16, tight, s, a) == hipSuccess ? LIPCACHE_OK : LIPCACHE_EHIP;
   }
   const int E = 32;  // features per workgroup of the vector kernel (d > 512)
   const size_t lds = static_cast<size_t>(E) * (d + 4) * sizeof(float);
