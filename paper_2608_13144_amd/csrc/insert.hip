@@ -160,6 +160,36 @@ __global__ __launch_bounds__(kCopyThreads) void insert_copy_kernel(const InsertP
   }
 }
 
+// Appends rows src_of[0 .. count) of the sources (device memory) in that order.
+lipcache_status append_rows(lipcache_cache* c, const float* z_src, const int32_t* label_src, const float* r_src,
+                            const int64_t* src_of, int64_t count, hipStream_t s) {
+  // rows move as 16-byte vectors
+  if ((reinterpret_cast<uintptr_t>(z_src) & 15u) != 0 || (reinterpret_cast<uintptr_t>(c->z) & 15u) != 0 ||
+      (reinterpret_cast<uintptr_t>(c->zimg) & 7u) != 0)
+    return LIPCACHE_EINVAL;
+  if (count < 0 || c->n + count > c->capacity) return LIPCACHE_ECAPACITY;
+  if (count == 0) return LIPCACHE_OK;
+  InsertParams p;
+  p.z_src = z_src;
+  p.label_src = label_src;
+  p.r_src = r_src;
+  p.src_of = src_of;
+  p.count = count;
+  p.cz = c->z;
+  p.cimg = static_cast<uint16_t*>(c->zimg);
+  p.cr = c->r;
+  p.clabel = c->label;
+  p.cnorm2 = c->norm2;
+  p.n0 = c->n;
+  p.d = c->d;
+  p.store = c->store_dtype;
+  hipLaunchKernelGGL(insert_copy_kernel, dim3(static_cast<unsigned>((count + kCopyWaves - 1) / kCopyWaves)),
+                     dim3(kCopyThreads), 0, s, p);
+  LC_LAUNCHED();
+  c->n += count;
+  return LIPCACHE_OK;
+}
+
 }  // namespace lc
 
 using namespace lc;
@@ -222,24 +252,8 @@ extern "C" lipcache_status lipcache_insert(lipcache_cache* c, const float* z_src
                        miss_selector, k, offsets, src_of);
     LC_LAUNCHED();
   }
-  InsertParams p;
-  p.z_src = z_src;
-  p.label_src = label_src;
-  p.r_src = r_src;
-  p.src_of = src_of;
-  p.count = host_total;
-  p.cz = c->z;
-  p.cimg = static_cast<uint16_t*>(c->zimg);
-  p.cr = c->r;
-  p.clabel = c->label;
-  p.cnorm2 = c->norm2;
-  p.n0 = c->n;
-  p.d = c->d;
-  p.store = c->store_dtype;
-  hipLaunchKernelGGL(insert_copy_kernel, dim3(static_cast<unsigned>((host_total + kCopyWaves - 1) / kCopyWaves)),
-                     dim3(kCopyThreads), 0, s, p);
-  LC_LAUNCHED();
-  c->n += host_total;
+  const lipcache_status st = append_rows(c, z_src, label_src, r_src, src_of, host_total, s);
+  if (st != LIPCACHE_OK) return st;
   if (inserted) *inserted = host_total;
   return LIPCACHE_OK;
 }

@@ -239,6 +239,11 @@ inline FilterSlack filter_slack(int precision, int store_dtype, int d_pad) {
   return f;
 }
 
+// Appends rows src_of[0 .. count) (device memory) of the sources to the cache
+// and advances c->n (insert.hip; nothing read back).
+lipcache_status append_rows(lipcache_cache* c, const float* z_src, const int32_t* label_src, const float* r_src,
+                            const int64_t* src_of, int64_t count, hipStream_t s);
+
 // Largest finite float: the threshold of a query or entry that passes the
 // filter against everything (-FLT_MAX) while +inf still marks rows that can
 // never be hit.
