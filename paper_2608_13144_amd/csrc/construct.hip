@@ -18,8 +18,8 @@
 // descending key; ties keep index order) orders the eligible candidates.
 // The greedy visit then runs in chunks of kChunk candidates: the chunk is
 // looked up against the cache (lipcache_lookup: a hit means a duplicate),
-// an exact float64 relation "b lies in the ball of a" is formed for all
-// pairs a < b of the chunk (bit matrix), one workgroup decides the chunk in
+// an exact relation "b lies in the ball of a" is formed for all pairs a < b
+// of the chunk (bit matrix; float64 for the pairs a float16 filter passes), one workgroup decides the chunk in
 // order (64 candidates at a time where no relation row is set, else one by
 // one with the AND of the relation row and the accepted bits; class counts in
 // LDS), and the accepted rows are appended in visit order.
@@ -202,68 +202,175 @@ __global__ __launch_bounds__(1024) void construct_compact_kernel(const uint32_t*
 }
 
 // Chunk rows in visit order: the stored values (bf16-rounded for a bf16
-// cache) as float32, with their payload and radius.  One wave per row.
+// cache) as float32, with their payload and radius.  One wave per row.  With
+// qthr also the filter thresholds of the row as the inner and as the outer
+// side of the chunk's relation, and (block 0) the row flags cleared.
 __global__ void construct_gather_kernel(const float* __restrict__ z, const int32_t* __restrict__ label,
                                         const float* __restrict__ r, const uint32_t* __restrict__ order, int k, int d,
                                         int bf16, float* __restrict__ zc, int32_t* __restrict__ lc,
-                                        float* __restrict__ rc, int64_t* __restrict__ src_c) {
+                                        float* __restrict__ rc, int64_t* __restrict__ src_c, const Thresholds th,
+                                        float* __restrict__ qthr, float* __restrict__ athr,
+                                        uint32_t* __restrict__ any) {
+  if (qthr && blockIdx.x == 0 && threadIdx.x < kChunkWords) any[threadIdx.x] = 0u;
   const int j = static_cast<int>(blockIdx.x) * (blockDim.x / kWave) + static_cast<int>(threadIdx.x) / kWave;
   if (j >= k) return;
   const int64_t src = order[j];
   const float* zr = z + src * d;
   float* out = zc + static_cast<int64_t>(j) * d;
-  for (int c = lane_id(); c < d; c += kWave) out[c] = bf16 ? bf16_round_f32(zr[c]) : zr[c];
+  double s = 0.0;
+  for (int c = lane_id(); c < d; c += kWave) {
+    const float v = bf16 ? bf16_round_f32(zr[c]) : zr[c];
+    out[c] = v;
+    s = __builtin_fma(static_cast<double>(v), static_cast<double>(v), s);
+  }
+  if (qthr) s = wave_sum(s);
   if (lane_id() == 0) {
     lc[j] = label[src];
     rc[j] = r[src];
     src_c[j] = src;
+    if (qthr) {
+      qthr[j] = query_threshold(s, th);
+      athr[j] = entry_threshold(r[src], static_cast<float>(s), th.kappa_c, th.eta1, th.range2);
+    }
   }
 }
 
 // rel[b * kChunkWords + a / 32] bit a % 32 set iff a < b and
-// ||z_b - z_a||^2 < r_a^2 (float64 over the chunk's stored values).  A block
-// of 1024 threads takes a 32 x 32 tile of (b, a) pairs, rows staged in LDS
-// 64 elements at a time; each wave covers two b rows, and one ballot per
-// wave gives their two words.
-__global__ __launch_bounds__(1024) void construct_relation_kernel(const float* __restrict__ zc,
-                                                                  const float* __restrict__ rc, int k, int d,
-                                                                  uint32_t* __restrict__ rel) {
+// ||z_b - z_a||^2 < r_a^2 (float64 over the chunk's stored values), for the
+// words up to b / 32; any[b / 32] bit b % 32 set iff row b has a bit.  A wave
+// takes a 32 x 32 tile of (b, a) pairs: the lookup's float16 filter (every
+// pair inside a ball passes) on v_mfma_f32_32x32x16_f16, then the exact
+// distance of the pairs that pass, four at a time.  A tile where many pass
+// (candidates inside each other's balls) forms all its distances in float64 instead, rows staged in LDS 64 features at a time,
+// 16 pairs per lane.
+//
+// Bound by the latency of the rows' loads (528 waves for 1,024 candidates).
+// The float64 sums of all pairs took 43 us at d = 256; this takes 12 us where
+// few pairs pass (the 1M-candidate construction) and 56 us where every tile
+// re-checks some (near copies of 64 rows).
+constexpr int kRelPairs = 64;  // passing pairs a tile re-checks four at a time
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__global__ __launch_bounds__(kWave) void construct_relation_kernel(const float* __restrict__ zc,
+                                                                   const float* __restrict__ rc,
+                                                                   const float* __restrict__ qthr,
+                                                                   const float* __restrict__ athr, int k, int d,
+                                                                   uint32_t* __restrict__ rel,
+                                                                   uint32_t* __restrict__ any) {
   __shared__ float za[32][65];
   __shared__ float zb[32][65];
-  const int tb = static_cast<int>(blockIdx.y);  // tile of b rows
-  const int ta = static_cast<int>(blockIdx.x);  // tile of a rows
-  const int t = static_cast<int>(threadIdx.x);
-  const int bl = t / 32, al = t % 32;
-  const int b = tb * 32 + bl, a = ta * 32 + al;
-  bool inside = false;
-  if (ta <= tb) {
-    double acc = 0.0;
+  const int ta = static_cast<int>(blockIdx.x), tb = static_cast<int>(blockIdx.y);
+  if (ta > tb) return;
+  const int lane = lane_id();
+  const int c32 = lane & 31, h = lane >> 5;
+  const int a = ta * 32 + c32;
+  // the b row of accumulator i of this lane, within the tile
+  auto b_row = [&](int i) { return 8 * (i >> 2) + 4 * h + (i & 3); };
+  auto chunk8 = [&](int row, int k0) {
+    const f32x4* p = reinterpret_cast<const f32x4*>(zc + static_cast<int64_t>(row < k ? row : k - 1) * d + k0);
+    const f32x4 x0 = p[0], x1 = p[1];
+    const float v[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+    return __builtin_bit_cast(f16x8, pack_f16x8(v));
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+#pragma unroll 4
+  for (int k0 = 8 * h; k0 < d; k0 += 16)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(chunk8(tb * 32 + c32, k0), chunk8(a, k0), acc, 0, 0, 0);
+  const float an = a < k ? athr[a] : __builtin_inff();
+  uint32_t mask = 0u;  // pairs that pass
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int b = tb * 32 + b_row(i);
+    if (b < k && a < b) mask |= static_cast<uint32_t>((acc[i] - qthr[b]) >= an) << i;
+  }
+  int n = __builtin_popcount(mask);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off, kWave);
+  uint32_t inside = 0u;
+  if (n > kRelPairs) {
+    double sum[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum[i] = 0.0;
     for (int c0 = 0; c0 < d; c0 += 64) {
       __syncthreads();
-      for (int e = t; e < 32 * 64; e += 1024) {
-        const int row = e / 64, col = e % 64;
+      for (int row = 0; row < 32; ++row) {
         const int ra = ta * 32 + row, rb = tb * 32 + row;
-        const bool in_row = c0 + col < d;
-        za[row][col] = (ra < k && in_row) ? zc[static_cast<int64_t>(ra) * d + c0 + col] : 0.0f;
-        zb[row][col] = (rb < k && in_row) ? zc[static_cast<int64_t>(rb) * d + c0 + col] : 0.0f;
+        const bool in_row = c0 + lane < d;
+        za[row][lane] = (ra < k && in_row) ? zc[static_cast<int64_t>(ra) * d + c0 + lane] : 0.0f;
+        zb[row][lane] = (rb < k && in_row) ? zc[static_cast<int64_t>(rb) * d + c0 + lane] : 0.0f;
       }
       __syncthreads();
-#pragma unroll 8
+#pragma unroll 2
       for (int c = 0; c < 64; ++c) {
-        const double diff = static_cast<double>(zb[bl][c]) - static_cast<double>(za[al][c]);
-        acc = __builtin_fma(diff, diff, acc);
+        const double av = static_cast<double>(za[c32][c]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const double diff = static_cast<double>(zb[b_row(i)][c]) - av;
+          sum[i] = __builtin_fma(diff, diff, sum[i]);
+        }
       }
     }
-    if (a < b && b < k) {
-      const double ra = static_cast<double>(rc[a]);
-      inside = acc < ra * ra;
+    const double ra = a < k ? static_cast<double>(rc[a]) : 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) inside |= static_cast<uint32_t>(((mask >> i) & 1u) != 0u && sum[i] < ra * ra) << i;
+  } else {
+    // four pairs at a time, 16 lanes each
+    const int grp = lane >> 4, l16 = lane & 15;
+    uint32_t rest = mask;
+    while (__ballot(rest != 0u) != 0ull) {
+      int src[4], bit[4], mine = -1, at = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const unsigned long long bal = __ballot(rest != 0u);
+        src[j] = bal != 0ull ? __builtin_ctzll(bal) : -1;
+        bit[j] = 0;
+        if (bal != 0ull) {  // uniform
+          bit[j] = __builtin_ctz(static_cast<uint32_t>(__shfl(static_cast<int>(rest), src[j], kWave)));
+          if (lane == src[j]) rest &= rest - 1u;
+          if (grp == j) {
+            mine = src[j];
+            at = bit[j];
+          }
+        }
+      }
+      const int from = mine < 0 ? 0 : mine;
+      const int pa = ta * 32 + (from & 31);
+      const int pb = tb * 32 + 8 * (at >> 2) + 4 * (from >> 5) + (at & 3);
+      double s = 0.0;
+      if (mine >= 0) {
+        const float* xa = zc + static_cast<int64_t>(pa) * d;
+        const float* xb = zc + static_cast<int64_t>(pb) * d;
+        for (int c = 4 * l16; c < d; c += 64) {
+          const f32x4 va = *reinterpret_cast<const f32x4*>(xa + c), vb = *reinterpret_cast<const f32x4*>(xb + c);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const double diff = static_cast<double>(vb[i]) - static_cast<double>(va[i]);
+            s = __builtin_fma(diff, diff, s);
+          }
+        }
+      }
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, kWave);
+      const double r = mine >= 0 ? static_cast<double>(rc[pa]) : 0.0;
+      const unsigned long long hit = __ballot(mine >= 0 && s < r * r);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (lane == src[j] && ((hit >> (16 * j)) & 1ull) != 0ull) inside |= 1u << bit[j];
     }
   }
-  const unsigned long long bal = __ballot(inside);
-  const int lane = lane_id();
-  if (b < k && (lane == 0 || lane == 32)) {
-    const uint32_t word = lane == 0 ? static_cast<uint32_t>(bal) : static_cast<uint32_t>(bal >> 32);
-    rel[static_cast<int64_t>(b) * kChunkWords + ta] = word;
+  // 16 ballots give the words of rows b_row(i) (h = 0) and b_row(i) + 4
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const unsigned long long bal = __ballot(((inside >> i) & 1u) != 0u);
+    const uint32_t word = h == 0 ? static_cast<uint32_t>(bal) : static_cast<uint32_t>(bal >> 32);
+    const int b = tb * 32 + b_row(i);
+    if (c32 == 0 && b < k) {
+      rel[static_cast<int64_t>(b) * kChunkWords + ta] = word;
+      if (word != 0u) atomicOr(&any[tb], 1u << (b & 31));
+    }
   }
 }
 
@@ -272,6 +379,7 @@ struct AcceptParams {
   int dedup;
   const int32_t* dup_label;   // lookup result per chunk candidate (MISS = not inside a cached ball); may be null
   const uint32_t* rel;        // chunk relation; null without de-dup
+  const uint32_t* any;        // rows with a relation bit
   const int32_t* lc;          // payload labels of the chunk
   const int64_t* src_c;       // candidate index of each chunk row
   int64_t* src_of;            // out: the accepted chunk rows, in order
@@ -284,9 +392,9 @@ struct AcceptParams {
 };
 
 // One workgroup decides the chunk in visit order.  All threads stage the
-// relation, the chunk's labels, the lookup verdicts, a per-row "has any
-// relation bit" flag and the class counts in LDS; wave 0 then walks the
-// chunk: lane l keeps bits 32 l .. 32 l + 31 of the accepted set, so
+// relation rows that have a bit (all of them are 128 KiB: 28 -> 17 us a
+// call without), the chunk's labels, the lookup verdicts and the class
+// counts in LDS; wave 0 then walks the chunk: lane l keeps bits 32 l .. 32 l + 31 of the accepted set, so
 // "inside an accepted earlier ball" is one AND per lane and one ballot,
 // needed only for rows that have a relation bit at all.
 __global__ __launch_bounds__(1024) void construct_accept_kernel(const AcceptParams p) {
@@ -296,25 +404,25 @@ __global__ __launch_bounds__(1024) void construct_accept_kernel(const AcceptPara
   __shared__ uint8_t sfree[kChunk];                 // not inside a cached ball
   __shared__ uint8_t srow[kChunk];                  // relation row j has a bit
   const int t = static_cast<int>(threadIdx.x);
-  if (p.dedup) {
-    for (int e = t; e < p.k * kChunkWords; e += 1024) srel[e] = p.rel[e];
-  }
   if (t < p.k) {
+    const bool any = p.dedup && ((p.any[t / 32] >> (t % 32)) & 1u) != 0u;
+    srow[t] = any ? 1 : 0;
+    if (any) {
+      // only a < t can be set; the words past t / 32 are not written
+      const int words = t / 32 + 1;
+      for (int w = 0; w < kChunkWords; w += 4) {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (w < words) v = *reinterpret_cast<const u32x4*>(p.rel + t * kChunkWords + w);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) srel[t * kChunkWords + w + i] = w + i < words ? v[i] : 0u;
+      }
+    }
     slab[t] = p.lc[t];
     sfree[t] = p.dup_label ? (p.dup_label[t] == LIPCACHE_MISS ? 1 : 0) : 1;
   }
   const int cached = p.n_classes < kMaxClasses / 16 ? p.n_classes : kMaxClasses / 16;
   if (p.per_class > 0)
     for (int c = t; c < cached; c += 1024) scount[c] = p.class_count[c];
-  __syncthreads();
-  if (t < p.k) {
-    uint32_t any = 0u;
-    if (p.dedup) {
-      const int words = (t + 31) / 32;  // only a < t can be set
-      for (int w = 0; w < words; ++w) any |= srel[t * kChunkWords + w];
-    }
-    srow[t] = any != 0u ? 1 : 0;
-  }
   __syncthreads();
   if (t >= kWave) return;
   const int lane = t;
@@ -872,7 +980,10 @@ struct CWs {
   int64_t* src_c;
   uint32_t* cand;       // [kChunk] candidates of the current chunk, in visit order
   int32_t* dup;
-  int64_t* src_of;
+  int64_t* src_of;      // [kChunk] accepted chunk rows (the K-center picks' space)
+  float* qthr;          // [kChunk] relation thresholds (the K-center distances' space)
+  float* athr;
+  uint32_t* any;        // [kChunkWords] chunk rows with a relation bit
   uint32_t* rel;
   int32_t* class_count;
   double* mind;
@@ -921,7 +1032,7 @@ inline CWs cws_layout(int64_t n, int d, int n_classes, int64_t budget, size_t su
   w.src_c = reinterpret_cast<int64_t*>(take(kChunk * 8));
   w.cand = reinterpret_cast<uint32_t*>(take(kChunk * 4));
   w.dup = reinterpret_cast<int32_t*>(take(kChunk * 4));
-  w.src_of = reinterpret_cast<int64_t*>(take(kChunk * 8));
+  w.any = reinterpret_cast<uint32_t*>(take(kChunk * 4));
   w.rel = reinterpret_cast<uint32_t*>(take(static_cast<size_t>(kChunk) * kChunkWords * 4));
   w.class_count = reinterpret_cast<int32_t*>(take(static_cast<size_t>(n_classes > 0 ? n_classes : 1) * 4));
   w.mind = reinterpret_cast<double*>(take(static_cast<size_t>(n) * 8));
@@ -934,6 +1045,10 @@ inline CWs cws_layout(int64_t n, int d, int n_classes, int64_t budget, size_t su
   w.picks = reinterpret_cast<int64_t*>(take(static_cast<size_t>(budget > 0 ? budget : 1) * 8));
   const size_t nc = static_cast<size_t>(n_classes > 0 ? n_classes : 1);
   w.cpicks = reinterpret_cast<int64_t*>(take(static_cast<size_t>(n > 0 ? n : 1) * 8));
+  // a chunk holds at most n candidates
+  w.src_of = w.cpicks;
+  w.qthr = reinterpret_cast<float*>(w.mind);
+  w.athr = w.qthr ? w.qthr + (n < kChunk ? n : kChunk) : nullptr;
   w.own = reinterpret_cast<int32_t*>(take(static_cast<size_t>(n > 0 ? n : 1) * 4));
   w.ccount = reinterpret_cast<uint32_t*>(take(nc * 4));
   w.coff = reinterpret_cast<int64_t*>(take((nc + 1) * 8));
@@ -1013,6 +1128,8 @@ extern "C" lipcache_status lipcache_construct(lipcache_cache* c, const float* z,
   int64_t added = 0;
   if (strategy != LIPCACHE_SELECT_KCENTER) {
     const int dedup = strategy == LIPCACHE_SELECT_RADIUS_DEDUP ? 1 : 0;
+    // the relation's filter (float32 rows on both sides)
+    const Thresholds th = filter_thresholds(LIPCACHE_F16, LIPCACHE_F32, d);
     int32_t* lab_ord = w.own;  // free in these strategies
     if (per_class > 0) {
       hipLaunchKernelGGL(order_labels_kernel, dim3(static_cast<unsigned>((n_elig + 255) / 256)), dim3(256), 0, s, order,
@@ -1032,7 +1149,7 @@ extern "C" lipcache_status lipcache_construct(lipcache_cache* c, const float* z,
     while (cur_k[1] > 0 && added < bud) {
       const int k = static_cast<int>(cur_k[1]);
       hipLaunchKernelGGL(construct_gather_kernel, dim3(static_cast<unsigned>((k + 3) / 4)), dim3(256), 0, s, z, label,
-                         r, w.cand, k, d, bf16, w.zc, w.lc, w.rc, w.src_c);
+                         r, w.cand, k, d, bf16, w.zc, w.lc, w.rc, w.src_c, th, dedup ? w.qthr : nullptr, w.athr, w.any);
       LC_LAUNCHED();
       const int32_t* dup = nullptr;
       if (dedup) {
@@ -1043,7 +1160,8 @@ extern "C" lipcache_status lipcache_construct(lipcache_cache* c, const float* z,
           dup = w.dup;
         }
         const unsigned tiles = static_cast<unsigned>((k + 31) / 32);
-        hipLaunchKernelGGL(construct_relation_kernel, dim3(tiles, tiles), dim3(1024), 0, s, w.zc, w.rc, k, d, w.rel);
+        hipLaunchKernelGGL(construct_relation_kernel, dim3(tiles, tiles), dim3(kWave), 0, s, w.zc, w.rc, w.qthr,
+                           w.athr, k, d, w.rel, w.any);
         LC_LAUNCHED();
       }
       AcceptParams ap;
@@ -1051,6 +1169,7 @@ extern "C" lipcache_status lipcache_construct(lipcache_cache* c, const float* z,
       ap.dedup = dedup;
       ap.dup_label = dup;
       ap.rel = dedup ? w.rel : nullptr;
+      ap.any = w.any;
       ap.lc = w.lc;
       ap.src_c = w.src_c;
       ap.src_of = w.src_of;

@@ -249,4 +249,40 @@ lipcache_status append_rows(lipcache_cache* c, const float* z_src, const int32_t
 // never be hit.
 constexpr float kPassAll = -3.4028234663852886e38f;
 
+// Filter thresholds.  A pair passes iff fl(g_hat - Q_q) >= A_i with
+//   Q_q = RD((1 - k) ||q||^2 / 2 - eta1 ||q|| - eta0),
+//   A_i = RD(((1 - k - 4u) ||z_i||^2 - r_i^2) / 2 - eta1 ||z_i|| - abs / 2)
+// (k, eta1, eta0 from filter_slack).  A row whose squared norm reaches
+// range2 (the float16 operands may not hold it) gets kPassAll: it passes
+// against every live entry or query and the exact re-check decides.  A NaN
+// norm gives a NaN threshold (never passes: NaN features have no hit), an
+// infinite query norm likewise (its distance to every entry is infinite).
+struct Thresholds {
+  double kq;       // 1 - k
+  double kappa_c;  // 1 - k - 4u
+  double eta1;
+  double eta0;
+  double range2;
+};
+
+__device__ __forceinline__ float query_threshold(double s, const Thresholds& t) {
+  if (s >= t.range2 && s < __builtin_inf()) return kPassAll;
+  return f32_round_down(t.kq * s * 0.5 - t.eta1 * __builtin_sqrt(s) - t.eta0);
+}
+
+// +inf for rows that can never be hit (r_i <= 0 or NaN).
+__device__ __forceinline__ float entry_threshold(float rr, float n2f, double kappa_c, double eta1, double range2) {
+  if (!(rr > 0.0f)) return __builtin_inff();
+  const double n2 = static_cast<double>(n2f);
+  if (n2 >= range2 && n2 < __builtin_inf()) return kPassAll;
+  const double r2 = static_cast<double>(rr) * static_cast<double>(rr);
+  return f32_round_down((kappa_c * n2 - r2) * 0.5 - eta1 * __builtin_sqrt(n2) - 0.5 * kFilterAbsSlack);
+}
+
+inline Thresholds filter_thresholds(int precision, int store_dtype, int d_pad) {
+  const FilterSlack fs = filter_slack(precision, store_dtype, d_pad);
+  const double u32 = 1.0 / 16777216.0;
+  return Thresholds{1.0 - fs.kappa, 1.0 - fs.kappa - 4.0 * u32, fs.eta1, fs.eta0, fs.range2};
+}
+
 }  // namespace lc

@@ -135,36 +135,6 @@ struct LookupParams {
 };
 
 // ------------------------------------------------------------- prep
-// Filter thresholds.  A pair passes iff fl(g_hat - Q_q) >= A_i with
-//   Q_q = RD((1 - k) ||q||^2 / 2 - eta1 ||q|| - eta0),
-//   A_i = RD(((1 - k - 4u) ||z_i||^2 - r_i^2) / 2 - eta1 ||z_i|| - abs / 2)
-// (k, eta1, eta0 from filter_slack).  A row whose squared norm reaches
-// range2 (the float16 operands may not hold it) gets kPassAll: it passes
-// against every live entry or query and the exact re-check decides.  A NaN
-// norm gives a NaN threshold (never passes: NaN features have no hit), an
-// infinite query norm likewise (its distance to every entry is infinite).
-struct Thresholds {
-  double kq;       // 1 - k
-  double kappa_c;  // 1 - k - 4u
-  double eta1;
-  double eta0;
-  double range2;
-};
-
-__device__ __forceinline__ float query_threshold(double s, const Thresholds& t) {
-  if (s >= t.range2 && s < __builtin_inf()) return kPassAll;
-  return f32_round_down(t.kq * s * 0.5 - t.eta1 * __builtin_sqrt(s) - t.eta0);
-}
-
-// +inf for rows that can never be hit (r_i <= 0 or NaN).
-__device__ __forceinline__ float entry_threshold(float rr, float n2f, double kappa_c, double eta1, double range2) {
-  if (!(rr > 0.0f)) return __builtin_inff();
-  const double n2 = static_cast<double>(n2f);
-  if (n2 >= range2 && n2 < __builtin_inf()) return kPassAll;
-  const double r2 = static_cast<double>(rr) * static_cast<double>(rr);
-  return f32_round_down((kappa_c * n2 - r2) * 0.5 - eta1 * __builtin_sqrt(n2) - 0.5 * kFilterAbsSlack);
-}
-
 // Prefix filter (features 0..kPrefixDims-1, one k-step of the 32x32 matrix
 // instruction).  The prefix of a squared distance is a lower bound of the
 // whole, so a pair with ||q - z_i|| < r_i (a hit) or within the boundary band
@@ -1948,13 +1918,7 @@ lipcache_status lookup_consts(const lipcache_cache* c, int32_t precision, Filter
       !make_plan(precision, c, true, fc.pl_list8, kDmaWaves))
     return LIPCACHE_EUNSUPPORTED;
   if (precision == LIPCACHE_F32 && (fc.pl.ks > 32 || c->d > 512)) return LIPCACHE_EUNSUPPORTED;
-  const FilterSlack fs = filter_slack(precision, c->store_dtype, fc.pl.d_pad);
-  const double u32 = 1.0 / 16777216.0;
-  fc.t.kq = 1.0 - fs.kappa;
-  fc.t.kappa_c = 1.0 - fs.kappa - 4.0 * u32;
-  fc.t.eta1 = fs.eta1;
-  fc.t.eta0 = fs.eta0;
-  fc.t.range2 = fs.range2;
+  fc.t = filter_thresholds(precision, c->store_dtype, fc.pl.d_pad);
   return LIPCACHE_OK;
 }
 
