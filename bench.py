@@ -31,7 +31,6 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_TFLOPS = {"f16": 2500.0, "f32": 157.3}   # MI355X dense matrix peaks (fp16 = bf16 rate)
-PREFIX_DIMS = 16                               # features the prefix scan contracts for every pair
 METRIC = "certified lookups/s and query·entry pairs/s at N=1M cache, d=256, C=200"
 
 
@@ -190,7 +189,7 @@ def stream_bench(args, cfg) -> int:
         rounds.append({"round": t, "n": n_t, "round_ms": dt * 1e3, "lookup_ms": lk, "hits": hits, "inserted": ins})
         total_s += dt
         total_lk += lk * 1e-3
-        flops += 2.0 * B * n_t * (PREFIX_DIMS if pruned_t else d)
+        flops += 2.0 * B * n_t * (prefix_dims(cache, args) if pruned_t else d)
         log(f"round {t}: n={n_t} round {dt * 1e3:.2f} ms lookup {lk:.2f} ms hits {hits}/{B} inserted {ins}")
     achieved = flops / total_lk / 1e12
     peak = PEAK_TFLOPS[args.precision]
@@ -221,7 +220,7 @@ def stream_bench(args, cfg) -> int:
                      "frac": achieved / peak, "traffic": None,
                      "kernel": "lookup_prefix_kernel" if pruned_t else "lookup_dma_kernel",
                      "algorithmic": (f"sum over rounds of 2*B*n_t*d = {flops:.4e} flop" if not pruned_t else
-                                     f"sum over rounds of the prefix contraction 2*B*n_t*{PREFIX_DIMS} = "
+                                     f"sum over rounds of the prefix contraction 2*B*n_t*{prefix_dims(cache, args)} = "
                                      f"{flops:.4e} flop")},
         "cpu_baseline": None,
     }
@@ -594,9 +593,9 @@ def main() -> int:
     pruned_path = takes_prefix_scan(cache, B, args)
     flops = 2.0 * B * n0 * d
     if pruned_path:
-        # the matrix work every pair gets: the first 16 features (the pairs
+        # the matrix work every pair gets: the first features (the pairs
         # the prefix filter keeps are re-checked over all of them)
-        flops = 2.0 * B * n0 * PREFIX_DIMS
+        flops = 2.0 * B * n0 * prefix_dims(cache, args)
     achieved = flops / (lk * 1e-3) / 1e12
     peak = PEAK_TFLOPS[args.precision]
     out = {
@@ -626,8 +625,8 @@ def main() -> int:
                      "kernel": ("lookup_prefix_kernel (exact prefix filter + re-check of what passes)" if pruned_path
                                 else "lookup_dma_kernel (fused contraction + filter + re-check)"),
                      "algorithmic": (f"2*B*N*d = {flops:.4e} flop per launch" if not pruned_path else
-                                     f"prefix contraction 2*B*N*{PREFIX_DIMS} = {flops:.4e} flop per launch "
-                                     "(every pair is ruled out by its distance over 16 features or re-checked)")},
+                                     f"prefix contraction 2*B*N*{prefix_dims(cache, args)} = {flops:.4e} flop per launch "
+                                     "(every pair is ruled out by its distance over these features or re-checked)")},
         "cpu_baseline": None,
     }
     tr = measured_traffic(cfg.name, args.precision)
@@ -662,9 +661,17 @@ def main() -> int:
 
 def takes_prefix_scan(cache, B, args) -> bool:
     """Whether ``cache.lookup`` of B queries takes the prefix scan: on request,
-    or by itself for a large enough float16 lookup (LIPCACHE_LOOKUP_PRUNE)."""
-    large = (B + 511) // 512 * 512 * cache.n * (cache.d - 32) >= 1 << 33
-    return args.precision == "f16" and cache.lookup_prunes("f16") and (args.prune or large)
+    or by itself for a large enough lookup (LIPCACHE_LOOKUP_PRUNE)."""
+    pairs = (B + 511) // 512 * 512 * cache.n
+    if args.precision == "f32":
+        return cache.store == "f32" and cache.n >= 32768 and pairs * (cache.d - 32) >= 1 << 30
+    large = pairs * (cache.d - (52 if cache.d < 192 else 32)) >= 1 << 33
+    return cache.lookup_prunes("f16") and (args.prune or large)
+
+
+def prefix_dims(cache, args) -> int:
+    """Features the prefix scan contracts for every pair."""
+    return 32 if args.precision == "f16" and cache.d < 192 else 16
 
 
 def full_contraction_context(cache, zq, res, prefix_ms, args) -> dict:
@@ -678,7 +685,7 @@ def full_contraction_context(cache, zq, res, prefix_ms, args) -> dict:
 
     from paper_2608_13144_amd import _lib, api
 
-    lib, B, prec = _lib.load(), zq.shape[0], _lib.F16
+    lib, B, prec = _lib.load(), zq.shape[0], _lib.F32 if args.precision == "f32" else _lib.F16
     need = lib.lipcache_lookup_workspace_bytes(B, cache.n, cache.d, prec)
     ws = torch.empty(need, dtype=torch.uint8, device=zq.device)
     o = api.LookupResult(*(torch.empty_like(t) for t in (res.label, res.index, res.dist2, res.stats, res.band)))

@@ -61,7 +61,8 @@ typedef enum lipcache_status {
 enum { LIPCACHE_F32 = 0, LIPCACHE_BF16 = 1, LIPCACHE_F16 = 2 };
 
 /* Lookup option, ORed into `precision` (LIPCACHE_F16 | LIPCACHE_LOOKUP_PRUNE):
- * prefix pruning.  The squared distance over the first 16 features is a
+ * prefix pruning.  The squared distance over the first 16 features (32 for
+ * rows of d < 192) is a
  * lower bound of the full one (Eq. (13) sums non-negative terms), so a pair
  * whose prefix filter (the same rigorous slack, with the ball widened to
  * r_i (1 + 3e-5) so that every pair of the boundary band survives) rejects
@@ -76,9 +77,11 @@ enum { LIPCACHE_F32 = 0, LIPCACHE_BF16 = 1, LIPCACHE_F16 = 2 };
  * about 4 B + 4 n bytes (the entry thresholds padded to a multiple of 1024
  * rows).  A lookup without the option takes the same path by itself when
  * the cache is as above (any d >= 64), the lookup is large enough to gain
- * ((B rounded up to 512) n (d - 32) >= 2^33) and ws_bytes is at least the
- * option's workspace size; with the plain size it runs the full
- * contraction. */
+ * ((B rounded up to 512) n (d - 32) >= 2^33, with d - 52 for d < 192) and
+ * ws_bytes is at least the option's workspace size; with the plain size it
+ * runs the full contraction.  So does a lookup with the float32 filter on an
+ * F32 store, over the first 16 features in float32, where (B rounded up to
+ * 512) n (d - 32) >= 2^30. */
 #define LIPCACHE_LOOKUP_PRUNE 0x100
 
 /* Radius modes (policy component rho, Sec. 4.3): the conservative radius of

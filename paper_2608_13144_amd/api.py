@@ -166,7 +166,7 @@ class LipCache:
                prune: bool = False) -> LookupResult:
         """lipcache_lookup: nearest certified hit per query, or MISS (async).
         ``prune``: LIPCACHE_LOOKUP_PRUNE (prefix pruning; same answers; large
-        float16 lookups take it by themselves)."""
+        lookups take it by themselves)."""
         _need_cuda(zq, "zq", torch.float32, 2)
         if zq.shape[1] != self.d:
             raise ValueError("lookup: query width differs from the cache's d")
@@ -181,9 +181,8 @@ class LipCache:
                 torch.zeros(4, dtype=torch.int64, device=dev),
                 torch.empty(B, dtype=torch.uint8, device=dev) if want_band else None)
         prec = _PRECISION[precision] | (L.LOOKUP_PRUNE if prune else 0)
-        # the float16 lookup takes the prefix scan whenever the workspace holds it
-        room = prec | L.LOOKUP_PRUNE if precision == "f16" else prec
-        ws = self._workspace(lib.lipcache_lookup_workspace_bytes(B, self.n, self.d, room))
+        # a large lookup takes the prefix scan whenever the workspace holds it
+        ws = self._workspace(lib.lipcache_lookup_workspace_bytes(B, self.n, self.d, prec | L.LOOKUP_PRUNE))
         cs = self.cstruct()
         st = lib.lipcache_lookup(ctypes.byref(cs), _p(zq), B, prec, _p(out.label), _p(out.index), _p(out.dist2),
                                  _p(out.stats), _p(out.band), _p(ws), ws.numel(), _stream(dev))

@@ -91,7 +91,7 @@ struct LookupParams {
   double eta1;           // absolute slack per unit of ||z_i||
   double range2;         // ||z_i||^2 from which an entry passes against everything
   const float* athr;     // [n_pad] per-entry filter thresholds A_i (+inf past n)
-  // Prefix scan: thresholds of the filter over features 0..kPrefixDims-1
+  // Prefix scan: thresholds of the filter over the prefix of a row
   // (Q'_q per query, A'_i per entry, +inf past n); null in the other scans.
   const float* qthr_p;
   const float* athr_p;
@@ -103,6 +103,7 @@ struct LookupParams {
   unsigned long long* dn_count;
   int64_t dn_cap;
   int pf_qblock;
+  int pf_limit;  // pairs that may pass per wave of queries and kPrRows rows
   const void* cimg;      // rows streamed by the DMA kernel (float16 image or z)
   int n_qblocks;
   int64_t slice_len;
@@ -135,15 +136,14 @@ struct LookupParams {
 };
 
 // ------------------------------------------------------------- prep
-// Prefix filter (features 0..kPrefixDims-1, one k-step of the 32x32 matrix
-// instruction).  The prefix of a squared distance is a lower bound of the
+// Prefix filter (the first KP x 32 bytes of a row, KP = 1 or 2: 16 float16 or
+// 8 float32 features each).  The prefix of a squared distance is a lower bound of the
 // whole, so a pair with ||q - z_i|| < r_i (a hit) or within the boundary band
 // has a prefix below r_i^2 (1 + 1e-5)^2 < r_i^2 (1 + 3e-5); the thresholds are
-// those of the full filter with d_pad = kPrefixDims, the prefix norms, and
+// those of the full filter with d_pad = the prefix's features, its norms, and
 // that widened ball, so such a pair always passes.  A row whose full squared
 // norm reaches range2 passes (as in the full filter); a NaN or infinite query
 // norm never does (it has no hit).
-constexpr int kPrefixDims = 16;
 constexpr double kPrefixBand = 3e-5;
 
 __device__ __forceinline__ float prefix_query_threshold(double s, double sp, const Thresholds& t) {
@@ -152,18 +152,23 @@ __device__ __forceinline__ float prefix_query_threshold(double s, double sp, con
   return f32_round_down(t.kq * sp * 0.5 - t.eta1 * __builtin_sqrt(sp) - t.eta0);
 }
 
-// A'_i from the image's prefix norm s = ||f16(z_P)||^2 (the image is what the
-// scan streams: 32 bytes a row where the stored float32 prefix has 64).  Each
-// image value is z_k (1 + e) + t with |e| <= u and |t| <= 2^-14, so
-//   (sqrt(s) - 4 2^-14) / (1 + u) <= ||z_P|| <= (sqrt(s) + 4 2^-14) / (1 - u);
+// A'_i from the prefix norm s of the values the scan streams.  For the float16
+// filter that is the image (32 bytes a row where the stored float32 prefix has
+// 64): s = ||f16(z_P)||^2, each value z_k (1 + e) + t with |e| <= u and |t| <=
+// 2^-14, so with e = sqrt(dims) 2^-14
+//   (sqrt(s) - e) / (1 + u) <= ||z_P|| <= (sqrt(s) + e) / (1 - u);
 // the lower bound goes into the term that grows with the norm and the upper
 // one into the slack.  u = 0 for a bf16 store, exact in float16 above the
-// sub-normals.  Rows the image clamps have a norm past range2.
+// sub-normals.  Rows the image clamps have a norm past range2.  The float32
+// filter streams the stored values themselves (lo = hi = 1, eta = 0).
 struct PrefixNorm {
-  double lo;  // 1 / (1 + u), rounded down
-  double hi;  // 1 / (1 - u), rounded up
+  double lo;   // 1 / (1 + u), rounded down
+  double hi;   // 1 / (1 - u), rounded up
+  double eta;  // sqrt(dims) 2^-14
+  int mode;    // kModeF16 or kModeF32
+  int kp;      // 32-byte steps of the prefix
+  int dims;    // its features
 };
-constexpr double kPrefixEta = 4.0 / 16384.0;  // sqrt(kPrefixDims) 2^-14
 
 __device__ __forceinline__ float prefix_entry_threshold(float rr, float n2f, double s, const Thresholds& t,
                                                         const PrefixNorm& pn) {
@@ -172,23 +177,31 @@ __device__ __forceinline__ float prefix_entry_threshold(float rr, float n2f, dou
   if (n2 >= t.range2 && n2 < __builtin_inf()) return kPassAll;
   const double r2 = static_cast<double>(rr) * static_cast<double>(rr) * (1.0 + kPrefixBand);
   const double h = __builtin_sqrt(s);
-  const double lo = h > kPrefixEta ? (h - kPrefixEta) * pn.lo : 0.0;
-  const double hi = (h + kPrefixEta) * pn.hi;
+  const double lo = h > pn.eta ? (h - pn.eta) * pn.lo : 0.0;
+  const double hi = (h + pn.eta) * pn.hi;
   return f32_round_down((t.kappa_c * lo * lo - r2) * 0.5 - t.eta1 * hi - 0.5 * kFilterAbsSlack);
 }
 
-// Squared norm of the first kPrefixDims image values of row i, in float64.
-__device__ __forceinline__ double prefix_norm2(const void* img, int d, int64_t i) {
-  const uint4* row = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(img) + i * d);
-  const uint4 v0 = row[0], v1 = row[1];
-  const uint32_t w[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+// Squared norm, in float64, of what the scan streams of row i.
+__device__ __forceinline__ double prefix_norm2(const void* rows, const PrefixNorm& pn, int d, int64_t i) {
+  const uint4* row = reinterpret_cast<const uint4*>(static_cast<const unsigned char*>(rows) +
+                                                    i * d * (pn.mode == kModeF16 ? 2 : 4));
   double s = 0.0;
+  for (int c = 0; c < 2 * pn.kp; ++c) {
+    const uint4 v = row[c];
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const double lo = static_cast<double>(f16_to_f32(static_cast<uint16_t>(w[j])));
-    const double hi = static_cast<double>(f16_to_f32(static_cast<uint16_t>(w[j] >> 16)));
-    s = __builtin_fma(lo, lo, s);
-    s = __builtin_fma(hi, hi, s);
+    for (int j = 0; j < 4; ++j) {
+      if (pn.mode == kModeF16) {
+        const double lo = static_cast<double>(f16_to_f32(static_cast<uint16_t>(w[j])));
+        const double hi = static_cast<double>(f16_to_f32(static_cast<uint16_t>(w[j] >> 16)));
+        s = __builtin_fma(lo, lo, s);
+        s = __builtin_fma(hi, hi, s);
+      } else {
+        const double x = static_cast<double>(__builtin_bit_cast(float, w[j]));
+        s = __builtin_fma(x, x, s);
+      }
+    }
   }
   return s;
 }
@@ -212,7 +225,7 @@ struct PrepEntries {
   double* qnorm;                 // ||q||^2 in float64 of every query (nullable)
   uint16_t* zq16;                // float16 copy of the queries (nullable)
   // prefix scan (qthr_p == nullptr: off): Q'_q, A'_i [np_pad], their
-  // constants, the image, and the counters of its lists to clear
+  // constants, the rows the scan streams, and the counters of its lists to clear
   float* qthr_p;
   float* athr_p;
   int64_t np_pad;
@@ -233,7 +246,7 @@ __global__ void lookup_prep_kernel(const float* __restrict__ zq, int64_t B, int 
     const int64_t i = static_cast<int64_t>(blockIdx.x - qblocks) * kLkThreads + threadIdx.x;
     write_athr(i, pe.cr, pe.cnorm2, pe.n, pe.n_pad, t.kappa_c, t.eta1, t.range2, pe.athr);
     if (pe.athr_p && i < pe.np_pad)
-      pe.athr_p[i] = i < pe.n ? prefix_entry_threshold(pe.cr[i], pe.cnorm2[i], prefix_norm2(pe.cimg, d, i), pe.tp, pe.pn)
+      pe.athr_p[i] = i < pe.n ? prefix_entry_threshold(pe.cr[i], pe.cnorm2[i], prefix_norm2(pe.cimg, pe.pn, d, i), pe.tp, pe.pn)
                               : __builtin_inff();
     return;
   }
@@ -247,7 +260,7 @@ __global__ void lookup_prep_kernel(const float* __restrict__ zq, int64_t B, int 
   for (int k = lane_id(); k < d; k += kWave) {
     const float x = row[k];
     s = __builtin_fma(static_cast<double>(x), static_cast<double>(x), s);
-    if (k < kPrefixDims) sp = s;
+    if (k < pe.pn.dims) sp = s;
     if (pe.zq16) pe.zq16[q * d + k] = f16_bits(x);
   }
   s = wave_sum(s);
@@ -1322,34 +1335,43 @@ __global__ __launch_bounds__(NW * kWave, 2) void lookup_dma_kernel(const LookupP
 
 // ------------------------------------------------------------- prefix scan
 // Exact pruning of the contraction: the scan streams only the prefix of every
-// row (features 0..15 of the float16 image, 32 bytes a row) and forms one
-// k-step of v_mfma_f32_32x32x16_f16 per 32x32 block of pairs, accumulated onto
-// -Q'_q, so a block holds no hit and no boundary-band pair unless some
-// accumulator reaches A'_i.  The pairs that do go to the re-check queue.
+// row, KP steps of 32 bytes (16 features of the float16 image, or 8 of a
+// float32 store for the float32 filter), and forms KP k-steps of
+// v_mfma_f32_32x32x16_f16 (four times v_mfma_f32_32x32x2_f32, eight times the
+// matrix cycles) per 32x32 block of pairs, accumulated onto -Q'_q, so a block
+// holds no hit and no boundary-band pair unless some accumulator reaches A'_i.
+// The pairs that do go to the re-check queue.
 //
-// What bounds it: the vector pipe and the matrix pipe about equally.  A
-// 64-query wave spends 2 matrix instructions (64 cycles) and 17 vector ones
-// (68 cycles: one v_max3 per two accumulators and the compare) per 32-entry
-// column tile.  Sixteen features instead of 32 (16x16x32 instructions) halve
-// the matrix cycles and the LDS bytes per pair for the same vector work.  A
-// wave holds only the prefix of its queries, so four waves share a SIMD and
-// cover each other's matrix latency.
+// What bounds it: the vector pipe and the matrix pipe together (they overlap
+// little: 64 cycles of one beside 64 of the other take 96).  A 64-query wave
+// spends 2 KP matrix instructions (64 KP cycles) and 17 vector ones (68 cycles:
+// one v_max3 per two accumulators and the compare) per 32-entry column tile.
+// One float16 step instead of a 16x16x32 one over 32 features halves the matrix
+// cycles and the LDS bytes per pair for the same vector work.  A wave holds
+// only the prefix of its queries, so four waves share a SIMD and cover each
+// other's matrix latency.
 //
-// Workgroup: 8 waves over tiles of 1,024 rows (32 KiB, double-buffered).  EW
-// of them share the same 64 queries and take every EW-th column tile: 1 for
+// Measured (whole call, full contraction and scan): 11.57 and 1.33 ms at n =
+// 1,048,576, B = 32,768, d = 256 (one step; 0.83 PFLOP/s); 0.121 and 0.088 ms
+// at n = 65,536, B = 8,192, d = 128 (two steps), there 0.97 and 0.34 ms with
+// the float32 filter.
+//
+// Workgroup: 8 waves over tiles of 1,024 / KP rows (32 KiB, double-buffered).
+// EW of them share the same 64 queries and take every EW-th column tile: 1 for
 // batches past 256 queries, up to 8 for at most 64 queries, where the rows
 // are what there is to split.
 //
 // Where the prefix tells little (features that repeat, balls as wide as the
-// data) the re-checks would cost more than the full contraction: a re-checked
-// pair takes about as long as 1,500 contracted ones (0.5 ns against 0.33 ps a
-// pair over the whole chip at d = 256; both grow with d).  So the workgroup
-// counts the pairs that pass, and past one in 2,048 (32 per wave and tile) it
-// stops before settling the tile it is in and puts the rest of its slice on a
-// list, which the full kernel (same queue) works off right after.
-constexpr int kPrRows = 1024;               // rows per prefix tile
+// data) the re-checks would cost more than the full contraction: about 0.7 ns
+// a pair over the whole chip, against 0.33 ps a contracted pair at d = 256.  So
+// the workgroup counts the pairs that pass, and past half of the full
+// contraction's time (pf_limit) it stops before settling the tile it is in and
+// puts the rest of its slice on a list, which the full kernel (same queue)
+// works off right after.
+constexpr int kPrRows = 1024;               // slices are multiples of this; rows per tile of one step
 constexpr int kPrCol = 32;                  // rows per column tile
-constexpr int kPrSubs = kPrRows / kPrCol;   // column tiles per prefix tile
+constexpr int pr_rows(int kp) { return kPrRows / kp; }          // rows per prefix tile
+constexpr int pr_subs(int kp) { return pr_rows(kp) / kPrCol; }  // column tiles per prefix tile
 constexpr int kPrWaves = 8;
 constexpr int kPrThreads = kPrWaves * kWave;
 constexpr int kPrWaveQ = 64;                // queries per wave: two 32-row tiles
@@ -1357,63 +1379,100 @@ constexpr int kPrRT = 2;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// A lane brings 16 bytes of its row, the first or the second half of the
+// prefix: in float32, step j pairs features j and 4 + j.
+template <int MODE>
 __device__ __forceinline__ f32x16 mfma_prefix(u32x4 a, u32x4 b, f32x16 acc) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), acc, 0, 0,
-                                                0);
+  if constexpr (MODE == kModeF16) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), acc, 0,
+                                                  0, 0);
+  } else {
+    const f32x4 af = __builtin_bit_cast(f32x4, a), bf = __builtin_bit_cast(f32x4, b);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[0], bf[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[1], bf[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[2], bf[2], acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(af[3], bf[3], acc, 0, 0, 0);
+  }
 }
 
-// Copies rows [t0, t0 + kPrRows) of the prefix into an LDS tile (rows past
+// Copies rows [t0, t0 + pr_rows) of the prefix into an LDS tile (rows past
 // n repeat the last row: their thresholds are +inf) and their thresholds
-// A'_i.  The tile holds 32-row groups of 1 KiB, the first 16-byte chunk of
-// the 32 rows and then the second: lane l reads its operand at 16 l.
+// A'_i.  The tile holds 32-row groups, per group and step the first 16-byte
+// chunk of the 32 rows and then the second: lane l reads its operand at 16 l.
+template <int MODE, int KP>
 __device__ __forceinline__ void issue_prefix_tile(unsigned char* buf, float* athp_buf, const LookupParams& p,
                                                   int64_t t0, int wave) {
-  const int row_bytes = p.d * 2;
+  const int row_bytes = p.d * ModeTraits<MODE>::kElemBytes;
   const int lane = lane_id();
   const unsigned char* base = static_cast<const unsigned char*>(p.cimg) + t0 * static_cast<int64_t>(row_bytes);
   const int64_t left = p.n - t0;
-  const int last = left < kPrRows ? static_cast<int>(left) - 1 : kPrRows - 1;
+  const int last = left < pr_rows(KP) ? static_cast<int>(left) - 1 : pr_rows(KP) - 1;
 #pragma unroll
-  for (int j = 0; j < kPrSubs / kPrWaves; ++j) {
+  for (int j = 0; j < pr_subs(KP) / kPrWaves; ++j) {
     const int group = j * kPrWaves + wave;
     const int row = group * kPrCol + (lane & 31);
     const int rr = row < last ? row : last;
-    lds_copy<16>(base, static_cast<uint32_t>(rr * row_bytes + (lane >> 5) * 16), buf + group * (kPrCol * 32));
+#pragma unroll
+    for (int kp = 0; kp < KP; ++kp)
+      lds_copy<16>(base, static_cast<uint32_t>(rr * row_bytes + kp * 32 + (lane >> 5) * 16),
+                   buf + (group * KP + kp) * (kPrCol * 32));
   }
 #pragma unroll
-  for (int i = 0; i < kPrRows / kPrThreads; ++i) {
-    const int w = wave * (kPrRows / kPrThreads) + i;
+  for (int i = 0; i < pr_rows(KP) / kPrThreads; ++i) {
+    const int w = wave * (pr_rows(KP) / kPrThreads) + i;
     lds_copy<4>(p.athr_p + t0 + w * kWave, static_cast<uint32_t>(lane * 4),
                 static_cast<unsigned char*>(static_cast<void*>(athp_buf)) + w * kWave * 4);
   }
 }
 
+// One 32x32 block of one row tile of queries, started at -Q'_q.
+template <int MODE, int KP>
+__device__ __forceinline__ f32x16 prefix_block(const u32x4 (&a)[KP], const u32x4 (&b)[KP], const f32x16& start) {
+  f32x16 acc = mfma_prefix<MODE>(a[0], b[0], start);
+#pragma unroll
+  for (int kp = 1; kp < KP; ++kp) acc = mfma_prefix<MODE>(a[kp], b[kp], acc);
+  return acc;
+}
+
 // The pairs of one column tile that pass (bits as mask_row<32>), from the
-// tile's operand and thresholds.
-__device__ __forceinline__ uint32_t prefix_mask(u32x4 b, float an, const u32x4 (&a)[kPrRT], const f32x16 (&nq)[kPrRT]) {
+// tile's operands and thresholds.
+template <int MODE, int KP>
+__device__ __forceinline__ uint32_t prefix_mask(const u32x4 (&b)[KP], float an, const u32x4 (&a)[kPrRT][KP],
+                                                const f32x16 (&nq)[kPrRT]) {
   uint32_t mask = 0u;
 #pragma unroll
   for (int rt = 0; rt < kPrRT; ++rt) {
-    const f32x16 acc = mfma_prefix(a[rt], b, nq[rt]);
+    const f32x16 acc = prefix_block<MODE, KP>(a[rt], b, nq[rt]);
 #pragma unroll
     for (int i = 0; i < 16; ++i) mask |= static_cast<uint32_t>(acc[i] >= an) << (rt * 16 + i);
   }
   return mask;
 }
 
+// The operands of column tile `sub` of an LDS tile.
+template <int KP>
+__device__ __forceinline__ void prefix_operand(const unsigned char* buf, int sub, int lane, u32x4 (&b)[KP]) {
+#pragma unroll
+  for (int kp = 0; kp < KP; ++kp)
+    b[kp] = *reinterpret_cast<const u32x4*>(buf + (sub * KP + kp) * (kPrCol * 32) + lane * 16);
+}
+
 // Pairs that pass in the surviving column tiles `pass` of the LDS tile (all
-// lanes); a wave with more than half of its column tiles surviving is not
-// counted out.
+// lanes).  In float16 a wave with more than half of its column tiles surviving
+// is not counted out (the full contraction costs little more than counting); in
+// float32 it is (the full contraction is d / 16 scans).
+template <int MODE, int KP>
 __device__ __forceinline__ int prefix_count(const unsigned char* buf, const float* athp_buf, uint32_t pass,
-                                            const u32x4 (&a)[kPrRT], const f32x16 (&nq)[kPrRT]) {
-  if (__builtin_popcount(pass) > kPrSubs / 2) return 1 << 20;
+                                            const u32x4 (&a)[kPrRT][KP], const f32x16 (&nq)[kPrRT]) {
+  if (MODE == kModeF16 && __builtin_popcount(pass) > pr_subs(KP) / 2) return 1 << 20;
   const int lane = lane_id();
   int n = 0;
 #pragma unroll 1
   for (uint32_t m = pass; m != 0u; m &= m - 1u) {
     const int sub = __builtin_ctz(m);
-    n += __builtin_popcount(prefix_mask(*reinterpret_cast<const u32x4*>(buf + sub * (kPrCol * 32) + lane * 16),
-                                        athp_buf[sub * kPrCol + (lane & 31)], a, nq));
+    u32x4 b[KP];
+    prefix_operand<KP>(buf, sub, lane, b);
+    n += __builtin_popcount(prefix_mask<MODE, KP>(b, athp_buf[sub * kPrCol + (lane & 31)], a, nq));
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, kWave);
@@ -1433,13 +1492,17 @@ struct PrefixQueue {
 
 // A surviving column tile, rows [ebase, ebase + 32): its pairs found again
 // (the LDS tile may be gone) and queued.
-template <int STORE>
+template <int MODE, int STORE, int KP>
 __device__ __forceinline__ void prefix_survivor(const LookupParams& p, int64_t ebase, int64_t q0, int64_t qwave,
-                                                const u32x4 (&a)[kPrRT], const f32x16 (&nq)[kPrRT], PrefixQueue& pq) {
+                                                const u32x4 (&a)[kPrRT][KP], const f32x16 (&nq)[kPrRT], PrefixQueue& pq) {
   const int lane = lane_id();
   const int64_t e = ebase + (lane & 31);
-  const u32x4 b = load_chunk<kModeF16, LIPCACHE_F16>(p.cimg, e < p.n ? e : p.n - 1, p.d, (lane >> 5) * 8);
-  uint32_t mask = prefix_mask(b, p.athr_p[e], a, nq);
+  u32x4 b[KP];
+#pragma unroll
+  for (int kp = 0; kp < KP; ++kp)
+    b[kp] = load_chunk<MODE, MODE == kModeF16 ? LIPCACHE_F16 : LIPCACHE_F32>(
+        p.cimg, e < p.n ? e : p.n - 1, p.d, (2 * kp + (lane >> 5)) * ModeTraits<MODE>::kPerChunk);
+  uint32_t mask = prefix_mask<MODE, KP>(b, p.athr_p[e], a, nq);
   if (mask != 0u) {
     int slot = atomicAdd(&pq.n, __builtin_popcount(mask));
     for (; mask != 0u && slot < kPrQueue; mask &= mask - 1u, ++slot) {
@@ -1473,13 +1536,13 @@ static_assert(kPrQueue <= kPrThreads, "one pair per thread");
 
 // Column tiles ew, ew + EW, ... of one prefix tile against the wave's 64
 // queries; returns the wave-uniform mask of those where a pair passes.
-template <int EW>
+template <int MODE, int KP, int EW>
 __device__ __forceinline__ uint32_t prefix_tile(const unsigned char* buf, const float* athp_buf, int ew,
-                                                const u32x4 (&a)[kPrRT], const f32x16 (&nq)[kPrRT]) {
+                                                const u32x4 (&a)[kPrRT][KP], const f32x16 (&nq)[kPrRT]) {
   const int lane = lane_id();
-  const unsigned char* op = buf + ew * (kPrCol * 32) + lane * 16;
+  const unsigned char* op = buf + ew * (KP * kPrCol * 32);
   const float* at = athp_buf + ew * kPrCol + (lane & 31);
-  constexpr int kN = kPrSubs / EW;
+  constexpr int kN = pr_subs(KP) / EW;
   uint32_t pass = 0u;
   // -inf the compiler cannot see through: every maximum is one v_max3 (with
   // the constant, or starting from two accumulators, it adds two v_max that
@@ -1487,21 +1550,24 @@ __device__ __forceinline__ uint32_t prefix_tile(const unsigned char* buf, const 
   float lowest = -__builtin_inff();
   asm volatile("" : "+v"(lowest));
   lowest = __builtin_canonicalizef(lowest);
-  u32x4 bn = *reinterpret_cast<const u32x4*>(op);
+  u32x4 bn[KP];
+  prefix_operand<KP>(op, 0, lane, bn);
   float ann = at[0];
 #pragma unroll 4
   for (int s = 0; s < kN; ++s) {
     // the next column tile's operand and threshold are read a tile ahead
     // (past the last: the first again); the barrier keeps them there
-    const u32x4 b = bn;
+    u32x4 b[KP];
+#pragma unroll
+    for (int kp = 0; kp < KP; ++kp) b[kp] = bn[kp];
     const float an = ann;
     const int nx = s + 1 < kN ? s + 1 : 0;
-    bn = *reinterpret_cast<const u32x4*>(op + nx * (EW * kPrCol * 32));
+    prefix_operand<KP>(op, nx * EW, lane, bn);
     ann = at[nx * (EW * kPrCol)];
     __builtin_amdgcn_sched_barrier(0);
     f32x16 acc[kPrRT];
 #pragma unroll
-    for (int rt = 0; rt < kPrRT; ++rt) acc[rt] = mfma_prefix(a[rt], b, nq[rt]);
+    for (int rt = 0; rt < kPrRT; ++rt) acc[rt] = prefix_block<MODE, KP>(a[rt], b, nq[rt]);
     float mx = lowest;
 #pragma unroll
     for (int i = 0; i < 16 * kPrRT; ++i) mx = __builtin_fmaxf(mx, acc[i / 16][i % 16]);
@@ -1510,11 +1576,11 @@ __device__ __forceinline__ uint32_t prefix_tile(const unsigned char* buf, const 
   return pass << ew;
 }
 
-template <int STORE, int EW>
+template <int MODE, int STORE, int KP, int EW>
 __global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const LookupParams p) {
   // the thresholds first: their reads then fit the LDS instruction's offset
   struct Tiles {
-    float athp[2][kPrRows];
+    float athp[2][pr_rows(KP)];
     unsigned char buf[2][kPrRows * 32];
     int passed[2];  // pairs that passed, even and odd prefix tiles, running totals
     PrefixQueue pq;
@@ -1524,7 +1590,8 @@ __global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const Look
   auto& buf = sh.buf;
   auto& passed = sh.passed;
   constexpr int kQW = kPrWaves / EW;
-  constexpr int kLimit = kQW * 32;  // pairs that may pass per prefix tile
+  constexpr int kRows = pr_rows(KP);
+  const int limit = (kQW * p.pf_limit + KP - 1) / KP;  // pairs that may pass per prefix tile
 
   int64_t q0, qend, e_begin, e_end;
   block_work(p, kQW * kPrWaveQ, q0, qend, e_begin, e_end);
@@ -1536,14 +1603,17 @@ __global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const Look
   const bool active = qwave < p.B;  // else only copies
   if (threadIdx.x < 2) passed[threadIdx.x] = 0;
   if (threadIdx.x == 2) sh.pq.n = 0;
-  issue_prefix_tile(buf[0], athp[0], p, e_begin, wave);
+  issue_prefix_tile<MODE, KP>(buf[0], athp[0], p, e_begin, wave);
 
-  u32x4 a[kPrRT];
+  u32x4 a[kPrRT][KP];
   f32x16 nq[kPrRT];
 #pragma unroll
   for (int rt = 0; rt < kPrRT; ++rt) {
     const int64_t q = qwave + rt * 32 + (lane & 31);
-    a[rt] = load_chunk<kModeF16, LIPCACHE_F32>(p.zq, q < p.B ? q : p.B - 1, p.d, (lane >> 5) * 8);
+#pragma unroll
+    for (int kp = 0; kp < KP; ++kp)
+      a[rt][kp] = load_chunk<MODE, LIPCACHE_F32>(p.zq, q < p.B ? q : p.B - 1, p.d,
+                                                 (2 * kp + (lane >> 5)) * ModeTraits<MODE>::kPerChunk);
     // four consecutive queries per group (the array is padded to 64)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1556,11 +1626,11 @@ __global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const Look
   }
 
   int seen[2] = {0, 0};
-  int total = 0, allowed = kLimit;
+  int total = 0, allowed = limit;
   bool stopped = false;
   uint32_t pass = 0u;
   int64_t t0 = e_begin;
-  for (int cur = 0;; cur ^= 1, t0 += kPrRows) {
+  for (int cur = 0;; cur ^= 1, t0 += kRows) {
     wait_copies();
     __syncthreads();  // publishes tile t0 and the count of the tile before
     if (t0 > e_begin) {
@@ -1569,21 +1639,21 @@ __global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const Look
       const int now = uniform(passed[cur ^ 1]);
       total += now - seen[cur ^ 1];
       seen[cur ^ 1] = now;
-      allowed += kLimit;
+      allowed += limit;
       if (total > allowed) {
         stopped = true;
         break;
       }
     }
-    const bool more = t0 + kPrRows < e_end;
-    if (more) issue_prefix_tile(buf[cur ^ 1], athp[cur ^ 1], p, t0 + kPrRows, wave);
+    const bool more = t0 + kRows < e_end;
+    if (more) issue_prefix_tile<MODE, KP>(buf[cur ^ 1], athp[cur ^ 1], p, t0 + kRows, wave);
     // settle the tile before while this tile's operands are in LDS
     for (uint32_t m = pass; m != 0u; m &= m - 1u)
-      prefix_survivor<STORE>(p, t0 - kPrRows + __builtin_ctz(m) * kPrCol, q0, qwave, a, nq, sh.pq);
+      prefix_survivor<MODE, STORE, KP>(p, t0 - kRows + __builtin_ctz(m) * kPrCol, q0, qwave, a, nq, sh.pq);
     if (t0 >= e_end) break;
-    pass = active ? prefix_tile<EW>(buf[cur], athp[cur], ew, a, nq) : 0u;
+    pass = active ? prefix_tile<MODE, KP, EW>(buf[cur], athp[cur], ew, a, nq) : 0u;
     if (pass != 0u) {
-      const int n = prefix_count(buf[cur], athp[cur], pass, a, nq);
+      const int n = prefix_count<MODE, KP>(buf[cur], athp[cur], pass, a, nq);
       if (lane == 0) atomicAdd(&passed[cur], n);
     }
   }
@@ -1594,18 +1664,18 @@ __global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const Look
     const int xcd = static_cast<int>(blockIdx.x) % kXcds;
     const int64_t slot = static_cast<int64_t>(atomicAdd(&p.dn_count[xcd], 1ull)) + xcd * p.dn_cap;
     p.dn_work[slot] = q0 * (1ll << 24) + e_begin / p.slice_len;
-    p.dn_row[slot] = t0 - kPrRows;
+    p.dn_row[slot] = t0 - kRows;
   }
 }
 
-// The queue of a prefix scan: the full filter first (float16, all d features,
-// the full kernel's own instructions in its order, so its own dot products),
+// The queue of a prefix scan: the full filter first (all d features, the full
+// kernel's own instructions in its order, so its own dot products),
 // then the exact re-check of the pairs it passes.  A wave takes 16 pairs:
 // pair i is row i and column i of one 16x16 block, its dot product the
 // block's diagonal.  The filter reads half the bytes of the float64 sum and
 // drops most pairs the 16 features could not (and the counter keeps its
 // meaning: pairs both filters let through).  FOLD as kFoldQ.
-template <int SRC, bool FOLD>
+template <int MODE, int SRC, bool FOLD>
 __global__ __launch_bounds__(256) void recheck_prefix_kernel(const RecheckArgs p, const void* __restrict__ cimg,
                                                              const float* __restrict__ qthr,
                                                              const float* __restrict__ athr,
@@ -1637,9 +1707,9 @@ __global__ __launch_bounds__(256) void recheck_prefix_kernel(const RecheckArgs p
       for (int r = 0; r < 4; ++r) acc[r] = -qrow[r];
     }
 #pragma unroll 4
-    for (int k0 = g * 8; k0 < p.d; k0 += 32)
-      acc = mfma_step<kModeF16>(load_chunk<kModeF16, LIPCACHE_F32>(p.zq, q, p.d, k0),
-                                load_chunk<kModeF16, LIPCACHE_F16>(cimg, e, p.d, k0), acc);
+    for (int k0 = g * ModeTraits<MODE>::kPerChunk; k0 < p.d; k0 += ModeTraits<MODE>::kPerStep)
+      acc = mfma_step<MODE>(load_chunk<MODE, LIPCACHE_F32>(p.zq, q, p.d, k0),
+                            load_chunk<MODE, MODE == kModeF16 ? LIPCACHE_F16 : LIPCACHE_F32>(cimg, e, p.d, k0), acc);
     // lane (m16, g = m16 / 4) holds the diagonal element of pair m16
     float v = acc[0];
 #pragma unroll
@@ -1760,12 +1830,12 @@ hipError_t launch_lookup(int precision, int store, const Plan& pl, const LookupP
 }
 
 // The prefix scan, EW waves of a workgroup on the same 64 queries (prefix_ew).
-template <int STORE>
-hipError_t launch_prefix_store(int ew, const LookupParams& p, unsigned grid, hipStream_t s) {
+template <int MODE, int STORE, int KP>
+hipError_t launch_prefix_ew(int ew, const LookupParams& p, unsigned grid, hipStream_t s) {
   switch (ew) {
 #define LC_PCASE(E)                                                                                         \
   case E:                                                                                                   \
-    hipLaunchKernelGGL((lookup_prefix_kernel<STORE, E>), dim3(grid), dim3(kPrThreads), 0, s, p);            \
+    hipLaunchKernelGGL((lookup_prefix_kernel<MODE, STORE, KP, E>), dim3(grid), dim3(kPrThreads), 0, s, p);  \
     return hipGetLastError();
     LC_PCASE(1)
     LC_PCASE(2)
@@ -1776,31 +1846,51 @@ hipError_t launch_prefix_store(int ew, const LookupParams& p, unsigned grid, hip
   }
 }
 
-inline hipError_t launch_prefix(int store, int ew, const LookupParams& p, unsigned grid, hipStream_t s) {
-  return store == LIPCACHE_F32 ? launch_prefix_store<LIPCACHE_F32>(ew, p, grid, s)
-                               : launch_prefix_store<LIPCACHE_BF16>(ew, p, grid, s);
+// The float32 filter scans only a float32 store, two steps (prune_consts).
+inline hipError_t launch_prefix(int precision, int store, int kp, int ew, const LookupParams& p, unsigned grid,
+                                hipStream_t s) {
+  if (precision == LIPCACHE_F32) return launch_prefix_ew<kModeF32, LIPCACHE_F32, 2>(ew, p, grid, s);
+  if (kp == 1)
+    return store == LIPCACHE_F32 ? launch_prefix_ew<kModeF16, LIPCACHE_F32, 1>(ew, p, grid, s)
+                                 : launch_prefix_ew<kModeF16, LIPCACHE_BF16, 1>(ew, p, grid, s);
+  return store == LIPCACHE_F32 ? launch_prefix_ew<kModeF16, LIPCACHE_F32, 2>(ew, p, grid, s)
+                               : launch_prefix_ew<kModeF16, LIPCACHE_BF16, 2>(ew, p, grid, s);
 }
 
-template <int STORE>
-hipError_t launch_prefix_recheck(int ks, unsigned grid, hipStream_t s, const RecheckArgs& ra, const void* cimg,
-                                 const float* qthr, const float* athr, const int64_t* gpos, const int64_t* ge,
-                                 const unsigned long long* gcount, int64_t cap) {
-  if (ks <= 4) {
-    static_assert(kFoldQ<kModeF16, 4> && !kFoldQ<kModeF16, 8>, "the full kernel's filter by width");
-    hipLaunchKernelGGL((recheck_prefix_kernel<STORE, true>), dim3(grid), dim3(256), 0, s, ra, cimg, qthr, athr, gpos,
-                       ge, gcount, cap);
-  } else {
-    hipLaunchKernelGGL((recheck_prefix_kernel<STORE, false>), dim3(grid), dim3(256), 0, s, ra, cimg, qthr, athr, gpos,
-                       ge, gcount, cap);
-  }
+struct PrefixQueueArgs {
+  const void* cimg;
+  const float* qthr;
+  const float* athr;
+  const int64_t* gpos;
+  const int64_t* ge;
+  const unsigned long long* gcount;
+  int64_t cap;
+};
+
+template <int MODE, int STORE, bool FOLD>
+hipError_t launch_prefix_recheck_as(unsigned grid, hipStream_t s, const RecheckArgs& ra, const PrefixQueueArgs& q) {
+  hipLaunchKernelGGL((recheck_prefix_kernel<MODE, STORE, FOLD>), dim3(grid), dim3(256), 0, s, ra, q.cimg, q.qthr,
+                     q.athr, q.gpos, q.ge, q.gcount, q.cap);
   return hipGetLastError();
+}
+
+inline hipError_t launch_prefix_recheck(int precision, int store, int ks, unsigned grid, hipStream_t s,
+                                        const RecheckArgs& ra, const PrefixQueueArgs& q) {
+  static_assert(kFoldQ<kModeF16, 4> && !kFoldQ<kModeF16, 8> && !kFoldQ<kModeF32, 2>, "the full kernel's filter");
+  if (precision == LIPCACHE_F32) return launch_prefix_recheck_as<kModeF32, LIPCACHE_F32, false>(grid, s, ra, q);
+  if (store == LIPCACHE_F32)
+    return ks <= 4 ? launch_prefix_recheck_as<kModeF16, LIPCACHE_F32, true>(grid, s, ra, q)
+                   : launch_prefix_recheck_as<kModeF16, LIPCACHE_F32, false>(grid, s, ra, q);
+  return ks <= 4 ? launch_prefix_recheck_as<kModeF16, LIPCACHE_BF16, true>(grid, s, ra, q)
+                 : launch_prefix_recheck_as<kModeF16, LIPCACHE_BF16, false>(grid, s, ra, q);
 }
 
 // Waves that share 64 queries: the fewest query blocks the batch fills.
 inline int prefix_ew(int64_t B) { return B <= kPrWaveQ ? 8 : B <= 2 * kPrWaveQ ? 4 : B <= 4 * kPrWaveQ ? 2 : 1; }
 
-inline hipError_t launch_dense(int store, const Plan& pl, const LookupParams& p, hipStream_t s) {
+inline hipError_t launch_dense(int precision, int store, const Plan& pl, const LookupParams& p, hipStream_t s) {
   const unsigned grid = 256;  // one workgroup per CU, all of them drain the lists
+  if (precision == LIPCACHE_F32) return launch_ks<kModeF32, LIPCACHE_F32, kVarDense>(pl, p, grid, s);
   return store == LIPCACHE_F32 ? launch_ks<kModeF16, LIPCACHE_F32, kVarDense>(pl, p, grid, s)
                                : launch_ks<kModeF16, LIPCACHE_BF16, kVarDense>(pl, p, grid, s);
 }
@@ -1905,8 +1995,8 @@ struct FilterConsts {
   Plan pl_list8;   // work-list scan: 8-wave blocks (long cluster lists)
   Thresholds t;
   bool prune = false;  // prefix scan (thresholds tp, image norm bounds pn)
-  Thresholds tp;
-  PrefixNorm pn;
+  Thresholds tp{};
+  PrefixNorm pn{};
 };
 
 // Precision argument: the filter precision, optionally | LIPCACHE_LOOKUP_PRUNE.
@@ -1922,42 +2012,61 @@ lipcache_status lookup_consts(const lipcache_cache* c, int32_t precision, Filter
   return LIPCACHE_OK;
 }
 
-// The prefix scan runs on the float16 image for rows of at least two k-steps,
-// on caches of at least kPruneMinRows rows (fewer fill too few 1024-row prefix
-// tiles to pay for the prefix thresholds).
+// The prefix scan runs on the float16 image, or on a float32 store for the
+// float32 filter, for rows of at least two k-steps, on caches of at least
+// kPruneMinRows rows (fewer fill too few 1024-row prefix tiles to pay for the
+// prefix thresholds).
 constexpr int64_t kPruneMinRows = 32 * kPrRows;
 
+// Steps of 32 bytes the scan contracts.  Two where one rules out too little:
+// float32 (8 features), and narrow rows, whose balls are wide against 16
+// features.  Measured (float16, n = 65,536, B = 8,192, C = 10, sigma = 0.5,
+// two data sets; one step, two steps, full contraction):
+//   d =  64  78 - 142 us    85 us        78 us
+//   d = 128 104 - 218 us    88 us       121 us
+//   d = 256  75 -  77 us      -         223 us
+// (1 to 4 pairs in 10,000 pass 16 features of the narrow rows, 2 in 100,000
+// pass 32.)  Where one step is enough at d = 128 it is the faster one (C =
+// 100, n = 262,139, B = 16,001: 225 and 336 us, 740 full), but the sizes do
+// not tell these data apart.
+inline int prefix_steps(bool f32, int d) { return f32 || d < 192 ? 2 : 1; }
+
 // Whether a lookup that does not ask for the prefix scan takes it: the matrix
-// work it saves, (B rounded up to the full kernel's 512 queries) n (d - 32),
-// against the launch and the prefix thresholds it adds.  Measured over d =
-// 64 .. 512, n = 32K .. 262K, B = 1 .. 8,192 (full against prefix scan): even
-// at 2^33 (d = 64, n = 262,144, B = 1,024: 47.1 and 47.3 us; d = 256, n =
-// 65,536, B <= 512: 49 and 34-40 us), 5 us slower at a quarter of it (34.8
-// and 39.7 us, launches), 1.5x faster at four times it and 9x at the headline.
-inline bool prefix_pays(int64_t B, int64_t n, int d) {
-  const double b = static_cast<double>((B + 511) / 512 * 512);
-  return b * static_cast<double>(n) * static_cast<double>(d - kPrefixDims * 2) >= 8589934592.0;
+// work it saves, (B rounded up to the full kernel's 512 queries) n times d less
+// what the scan costs (32 features for one step, 52 for two), against the
+// launch and the prefix thresholds it adds.  Measured over d = 64 .. 512, n =
+// 32K .. 262K, B = 1 .. 8,192 (full against prefix scan): d = 256, n = 65,536,
+// B <= 512 (just above 2^33): 49 and 34-40 us; 5 us slower at a quarter of it
+// (34.8 and 39.7 us, launches); two steps at d = 64, B = 8,192: 78 and 85 us
+// at n = 65,536 (0.75 2^33), 222 and 197 at n = 262,144; 9x at the headline.
+// The float32 filter spends 12 to 16 times the time per feature: from an
+// eighth of that work on.
+inline bool prefix_pays(int32_t precision, int64_t B, int64_t n, int d) {
+  const double pairs = static_cast<double>((B + 511) / 512 * 512) * static_cast<double>(n);
+  if (precision == LIPCACHE_F32) return pairs * static_cast<double>(d - 32) >= 1073741824.0;
+  return pairs * static_cast<double>(d - (prefix_steps(false, d) == 2 ? 52 : 32)) >= 8589934592.0;
 }
 
 void prune_consts(const lipcache_cache* c, int32_t precision, FilterConsts& fc) {
-  fc.prune = precision == LIPCACHE_F16 && c->zimg != nullptr && fc.pl.ks >= 2 && c->n >= kPruneMinRows;
+  const bool f32 = precision == LIPCACHE_F32;
+  fc.prune = (f32 ? c->store_dtype == LIPCACHE_F32 : c->zimg != nullptr) && fc.pl.ks >= 2 && c->n >= kPruneMinRows;
   if (!fc.prune) return;
-  const FilterSlack fs = filter_slack(precision, c->store_dtype, kPrefixDims);
-  const double u32 = 1.0 / 16777216.0;
+  const int kp = prefix_steps(f32, c->d);
+  const int dims = kp * (f32 ? 8 : 16);
   // The prefix accumulation starts at -Q'_q, which adds gam |Q'_q| to its
-  // rounding error (gam for the kPrefixDims products and the start value):
+  // rounding error (gam for the products and the start value):
   // Q'_q = RD((1 - kappa - gam) s / 2 - (1 + 2 gam)(eta1 sqrt(s) + eta0))
   // keeps every pair the unfolded test would pass, for either sign of Q'_q.
-  const double n = static_cast<double>(kPrefixDims) + 2.0;
-  const double gam = n * u32 / (1.0 - n * u32);
-  fc.tp.kq = 1.0 - fs.kappa - gam;
-  fc.tp.kappa_c = 1.0 - fs.kappa - 4.0 * u32;
-  fc.tp.eta1 = fs.eta1 * (1.0 + 2.0 * gam);
-  fc.tp.eta0 = fs.eta0 * (1.0 + 2.0 * gam);
-  fc.tp.range2 = fs.range2;
-  const double u = c->store_dtype == LIPCACHE_BF16 ? 0.0 : 1.0 / 2048.0;
-  fc.pn.lo = (1.0 - 1e-15) / (1.0 + u);
-  fc.pn.hi = (1.0 + 1e-15) / (1.0 - u);
+  const double n = static_cast<double>(dims) + 2.0;
+  const double gam = n / 16777216.0 / (1.0 - n / 16777216.0);
+  fc.tp = filter_thresholds(precision, c->store_dtype, dims);
+  fc.tp.kq -= gam;
+  fc.tp.eta1 *= 1.0 + 2.0 * gam;
+  fc.tp.eta0 *= 1.0 + 2.0 * gam;
+  const double u = f32 || c->store_dtype == LIPCACHE_BF16 ? 0.0 : 1.0 / 2048.0;
+  fc.pn = PrefixNorm{(1.0 - 1e-15) / (1.0 + u), (1.0 + 1e-15) / (1.0 - u),
+                     f32 ? 0.0 : (1.0 + 1e-15) * __builtin_sqrt(static_cast<double>(dims)) / 16384.0,
+                     f32 ? kModeF32 : kModeF16, kp, dims};
 }
 
 // Stage 1: Q_q, and the reset of best / band flags / counters; with `view`
@@ -1978,6 +2087,7 @@ lipcache_status lookup_stage_prep(const float* zq, int64_t B, int d, const Filte
     pe = PrepEntries{view->r, view->norm2, view->n, athr_len(view->n), athr, gq_count, qnorm, zq16,
                      pr ? qthr_p : nullptr, pr ? athr_p : nullptr, pr ? athp_len(view->n) : 0, view->zimg,
                      fc.tp, fc.pn, pr ? gq_count + 1 : nullptr};
+    if (fc.pn.mode == kModeF32) pe.cimg = view->z;
     const int64_t cover = pe.np_pad > pe.n_pad ? pe.np_pad : pe.n_pad;
     eblocks = (cover + kLkThreads - 1) / kLkThreads;
   }
@@ -2046,6 +2156,7 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
   p.dn_count = nullptr;
   p.dn_cap = 0;
   p.pf_qblock = 0;
+  p.pf_limit = 0;
   int64_t grid = n_items;
   p.slice_len = 0;
   const bool prune = qthr_p && athr_p && !items && !dump;
@@ -2055,6 +2166,9 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
     // turns of the chip (two workgroups per CU) while a slice keeps four
     // tiles, and one turn while it keeps one.
     p.pf_qblock = kPrWaves / ew * kPrWaveQ;
+    // half of the full contraction's time in re-checks (64 x 1,024 pairs at
+    // 1.3 fs a feature in float16 and 16 in float32, 0.7 ns a re-check)
+    p.pf_limit = precision == LIPCACHE_F32 ? view->d : view->d / 16;
     p.n_qblocks = static_cast<int>((B + p.pf_qblock - 1) / p.pf_qblock);
     const int64_t tiles = (view->n + kPrRows - 1) / kPrRows;
     const int64_t per8 = kXcds * static_cast<int64_t>(p.n_qblocks);
@@ -2099,10 +2213,10 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
   const hipError_t e = dump    ? launch_lookup<kVarDump>(precision, view->store_dtype, pl, p, gu, s)
                        : items ? (pl.waves == kListWaves ? launch_lookup<kVarList>(precision, view->store_dtype, pl, p, gu, s)
                                                          : launch_lookup<kVarList8>(precision, view->store_dtype, pl, p, gu, s))
-                       : prune ? launch_prefix(view->store_dtype, ew, p, gu, s)
+                       : prune ? launch_prefix(precision, view->store_dtype, fc.pn.kp, ew, p, gu, s)
                                : launch_lookup<kVarLookup>(precision, view->store_dtype, pl, p, gu, s);
   if (e != hipSuccess) return LIPCACHE_EHIP;
-  if (prune && launch_dense(view->store_dtype, pl, p, s) != hipSuccess) return LIPCACHE_EHIP;
+  if (prune && launch_dense(precision, view->store_dtype, pl, p, s) != hipSuccess) return LIPCACHE_EHIP;
   if (dump) return LIPCACHE_OK;
   // the pairs the scan's waves queued, one chip-wide pass
   const RecheckArgs ra{zq, view->z, view->r, best, bflag, stats, static_cast<int64_t>(LLONG_MAX), view->n, view->d,
@@ -2111,11 +2225,8 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
   if (blocks > 512) blocks = 512;
   if (prune) {
     const hipError_t er =
-        view->store_dtype == LIPCACHE_BF16
-            ? launch_prefix_recheck<LIPCACHE_BF16>(pl.ks, static_cast<unsigned>(blocks), s, ra, p.cimg, qthr, athr,
-                                                   gq.pos, gq.e, gq.count, gq_cap)
-            : launch_prefix_recheck<LIPCACHE_F32>(pl.ks, static_cast<unsigned>(blocks), s, ra, p.cimg, qthr, athr,
-                                                  gq.pos, gq.e, gq.count, gq_cap);
+        launch_prefix_recheck(precision, view->store_dtype, pl.ks, static_cast<unsigned>(blocks), s, ra,
+                              PrefixQueueArgs{p.cimg, qthr, athr, gq.pos, gq.e, gq.count, gq_cap});
     return er == hipSuccess ? LIPCACHE_OK : LIPCACHE_EHIP;
   }
   if (view->store_dtype == LIPCACHE_BF16) {
@@ -2188,8 +2299,8 @@ lipcache_status run_lookup(const lipcache_cache* c, const float* zq, int64_t B, 
   const size_t need = ws_layout(B, c->n, nullptr, nullptr, wants_prune(precision_arg));
   if (!ws || ws_bytes < need || !aligned256(ws)) return LIPCACHE_EWORKSPACE;
   // the prefix scan also without the option, where it pays and the workspace holds it
-  if (!dump && (wants_prune(precision_arg) || (prefix_pays(B, c->n, c->d) &&
-                                               ws_bytes >= ws_layout(B, c->n, nullptr, nullptr, true))))
+  if (!dump && ((wants_prune(precision_arg) && precision == LIPCACHE_F16) ||
+                (prefix_pays(precision, B, c->n, c->d) && ws_bytes >= ws_layout(B, c->n, nullptr, nullptr, true))))
     prune_consts(c, precision, fc);
   return lookup_on(c, zq, B, precision, fc, label_out, index_out, dist2_out, stats, band_flag, ws, s, dump, g_hat,
                    cand);
@@ -2337,7 +2448,7 @@ extern "C" int32_t lipcache_lookup_prunes(const lipcache_cache* c, int32_t preci
   FilterConsts fc;
   if (lookup_consts(c, precision, fc) != LIPCACHE_OK) return 0;
   prune_consts(c, precision, fc);
-  return fc.prune && fc.pl.ks <= 16 ? 1 : 0;
+  return fc.prune && precision == LIPCACHE_F16 && fc.pl.ks <= 16 ? 1 : 0;
 }
 
 extern "C" size_t lipcache_lookup_workspace_bytes(int64_t B, int64_t N, int32_t d, int32_t precision) {
@@ -2371,8 +2482,8 @@ extern "C" lipcache_status lipcache_lookup_noalloc(const lipcache_cache* c, cons
   const lipcache_status cs = lookup_consts(c, precision, fc);
   if (cs != LIPCACHE_OK) return cs;
   if (ws_layout(B, c->n, nullptr, nullptr, wants_prune(precision_arg)) > kNoAllocBytes) return LIPCACHE_EWORKSPACE;
-  if (wants_prune(precision_arg) ||
-      (prefix_pays(B, c->n, c->d) && ws_layout(B, c->n, nullptr, nullptr, true) <= kNoAllocBytes))
+  if ((wants_prune(precision_arg) && precision == LIPCACHE_F16) ||
+      (prefix_pays(precision, B, c->n, c->d) && ws_layout(B, c->n, nullptr, nullptr, true) <= kNoAllocBytes))
     prune_consts(c, precision, fc);
   void* ws = device_scratch();
   if (!ws) return LIPCACHE_EHIP;

@@ -21,11 +21,11 @@ from gpu_helpers import build_cache, compare_lookup, gpu, host, oracle_cache, sa
 pytestmark = pytest.mark.gpu
 
 
-def full_contraction(c, zq):
+def full_contraction(c, zq, prec=L.F16):
     """The lookup on the plain workspace: every pair's whole dot product."""
     lib = L.load()
     B = zq.shape[0]
-    need = lib.lipcache_lookup_workspace_bytes(B, c.n, c.d, L.F16)
+    need = lib.lipcache_lookup_workspace_bytes(B, c.n, c.d, prec)
     ws = torch.empty(need, dtype=torch.uint8, device=zq.device)
     out = api.LookupResult(torch.empty(B, dtype=torch.int32, device=zq.device),
                            torch.empty(B, dtype=torch.int64, device=zq.device),
@@ -34,7 +34,7 @@ def full_contraction(c, zq):
                            torch.empty(B, dtype=torch.uint8, device=zq.device))
     p = [ctypes.c_void_p(t.data_ptr()) for t in (zq, out.label, out.index, out.dist2, out.stats, out.band, ws)]
     cs = c.cstruct()
-    st = lib.lipcache_lookup(ctypes.byref(cs), p[0], B, L.F16, p[1], p[2], p[3], p[4], p[5], p[6], need,
+    st = lib.lipcache_lookup(ctypes.byref(cs), p[0], B, prec, p[1], p[2], p[3], p[4], p[5], p[6], need,
                              ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
     assert st == L.OK
     return out
@@ -82,17 +82,17 @@ def test_prefix_matches_oracle_and_full(B, n, d, store):
 
 @pytest.mark.parametrize("d,B,part", [(64, 700, 1.0), (256, 700, 0.5), (512, 300, 1.0), (768, 90, 0.5), (1024, 40, 1.0)])
 def test_prefix_without_information(d, B, part):
-    """Rows that share their first 16 features (all of them, or those of the
+    """Rows that share their first 32 features (all of them, or those of the
     second half, so that slices stop part way): the slices go to the full
     contraction, each pair once."""
     say("prefix without information", d, B, part)
     rng = np.random.default_rng(d + B)
     n = 40000
     z = rng.standard_normal((n, d)).astype(np.float32)
-    z[int(n * (1 - part)):, :16] = z[0, :16]
+    z[int(n * (1 - part)):, :32] = z[0, :32]
     st = oracle_cache(z, rng.integers(0, 5, n).astype(np.int32), np.full(n, 0.2 * math.sqrt(d), np.float32), d)
     zq = near_queries(rng, st, B, int(n * (1 - part)))
-    zq[:, :16] = z[0, :16]
+    zq[:, :32] = z[0, :32]
     c = build_cache(st)
     out = c.lookup(gpu(zq), prune=True)
     sa, sb = same_answers(out, full_contraction(c, gpu(zq)), f"d={d} B={B}")
@@ -101,6 +101,31 @@ def test_prefix_without_information(d, B, part):
     # every slice is handed over before a pair is settled
     if part == 1.0:
         assert sa[L.STAT_RECHECKED] == sb[L.STAT_RECHECKED]
+
+
+# the float32 filter scans 16 features of a float32 store; every size here is
+# one that takes the scan by itself
+@pytest.mark.parametrize("B,n,d,informative", [
+    (60, 200000, 96, True), (700, 70001, 64, True), (130, 40000, 128, True), (600, 33001, 288, True),
+    (700, 40000, 64, False), (300, 40000, 512, False),
+])
+def test_prefix_float32_filter(B, n, d, informative):
+    say("prefix float32", B, n, d, informative)
+    assert (B + 511) // 512 * 512 * n * (d - 32) >= 2**30
+    rng = np.random.default_rng(B + n + d)
+    z = rng.standard_normal((n, d)).astype(np.float32)
+    if not informative:
+        z[:, :16] = z[0, :16]
+    st = oracle_cache(z, rng.integers(0, 5, n).astype(np.int32), np.full(n, 0.1 * math.sqrt(d), np.float32), d)
+    zq = near_queries(rng, st, B)
+    if not informative:
+        zq[:, :16] = z[0, :16]
+    c = build_cache(st, image=False)
+    out = c.lookup(gpu(zq), precision="f32")
+    what = f"float32 B={B} n={n} d={d}"
+    same_answers(out, full_contraction(c, gpu(zq), L.F32), what)
+    compare_lookup(out, oracle.lookup_blocked(zq, st.z, st.r, st.label), what)
+    assert host(out.stats)[L.STAT_HITS] > B // 4
 
 
 def test_prefix_radius_infinite_and_dead():
