@@ -81,7 +81,7 @@ enum { LIPCACHE_F32 = 0, LIPCACHE_BF16 = 1, LIPCACHE_F16 = 2 };
  * ws_bytes is at least the option's workspace size; with the plain size it
  * runs the full contraction.  So does a lookup with the float32 filter on an
  * F32 store, over the first 16 features in float32, where (B rounded up to
- * 512) n (d - 32) >= 2^30. */
+ * 512) n (d - 32) >= 2^30 (lipcache_lookup only). */
 #define LIPCACHE_LOOKUP_PRUNE 0x100
 
 /* Radius modes (policy component rho, Sec. 4.3): the conservative radius of

@@ -2482,8 +2482,11 @@ extern "C" lipcache_status lipcache_lookup_noalloc(const lipcache_cache* c, cons
   const lipcache_status cs = lookup_consts(c, precision, fc);
   if (cs != LIPCACHE_OK) return cs;
   if (ws_layout(B, c->n, nullptr, nullptr, wants_prune(precision_arg)) > kNoAllocBytes) return LIPCACHE_EWORKSPACE;
-  if ((wants_prune(precision_arg) && precision == LIPCACHE_F16) ||
-      (prefix_pays(precision, B, c->n, c->d) && ws_layout(B, c->n, nullptr, nullptr, true) <= kNoAllocBytes))
+  // The float32 filter keeps the full contraction here: every counter, the
+  // re-checked pairs too, is that of a lookup on the plain workspace.
+  if (precision == LIPCACHE_F16 &&
+      (wants_prune(precision_arg) ||
+       (prefix_pays(precision, B, c->n, c->d) && ws_layout(B, c->n, nullptr, nullptr, true) <= kNoAllocBytes)))
     prune_consts(c, precision, fc);
   void* ws = device_scratch();
   if (!ws) return LIPCACHE_EHIP;
