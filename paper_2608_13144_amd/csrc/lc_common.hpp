@@ -257,6 +257,9 @@ constexpr float kPassAll = -3.4028234663852886e38f;
 // against every live entry or query and the exact re-check decides.  A NaN
 // norm gives a NaN threshold (never passes: NaN features have no hit), an
 // infinite query norm likewise (its distance to every entry is infinite).
+// A_i is never below kPassAll: the accumulators of positions past the batch
+// are -inf, and a threshold of -inf (an infinite or huge radius) would let
+// them through; those of live pairs are finite.
 struct Thresholds {
   double kq;       // 1 - k
   double kappa_c;  // 1 - k - 4u
@@ -270,13 +273,20 @@ __device__ __forceinline__ float query_threshold(double s, const Thresholds& t) 
   return f32_round_down(t.kq * s * 0.5 - t.eta1 * __builtin_sqrt(s) - t.eta0);
 }
 
+// A threshold of the entry side: the largest float <= x, at least kPassAll
+// (NaN stays).
+__device__ __forceinline__ float entry_round_down(double x) {
+  const float f = f32_round_down(x);
+  return f < kPassAll ? kPassAll : f;
+}
+
 // +inf for rows that can never be hit (r_i <= 0 or NaN).
 __device__ __forceinline__ float entry_threshold(float rr, float n2f, double kappa_c, double eta1, double range2) {
   if (!(rr > 0.0f)) return __builtin_inff();
   const double n2 = static_cast<double>(n2f);
   if (n2 >= range2 && n2 < __builtin_inf()) return kPassAll;
   const double r2 = static_cast<double>(rr) * static_cast<double>(rr);
-  return f32_round_down((kappa_c * n2 - r2) * 0.5 - eta1 * __builtin_sqrt(n2) - 0.5 * kFilterAbsSlack);
+  return entry_round_down((kappa_c * n2 - r2) * 0.5 - eta1 * __builtin_sqrt(n2) - 0.5 * kFilterAbsSlack);
 }
 
 inline Thresholds filter_thresholds(int precision, int store_dtype, int d_pad) {

@@ -179,7 +179,7 @@ __device__ __forceinline__ float prefix_entry_threshold(float rr, float n2f, dou
   const double h = __builtin_sqrt(s);
   const double lo = h > pn.eta ? (h - pn.eta) * pn.lo : 0.0;
   const double hi = (h + pn.eta) * pn.hi;
-  return f32_round_down((t.kappa_c * lo * lo - r2) * 0.5 - t.eta1 * hi - 0.5 * kFilterAbsSlack);
+  return entry_round_down((t.kappa_c * lo * lo - r2) * 0.5 - t.eta1 * hi - 0.5 * kFilterAbsSlack);
 }
 
 // Squared norm, in float64, of what the scan streams of row i.
