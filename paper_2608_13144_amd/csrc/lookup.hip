@@ -1503,6 +1503,15 @@ __device__ __forceinline__ void prefix_survivor(const LookupParams& p, int64_t e
     b[kp] = load_chunk<MODE, MODE == kModeF16 ? LIPCACHE_F16 : LIPCACHE_F32>(
         p.cimg, e < p.n ? e : p.n - 1, p.d, (2 * kp + (lane >> 5)) * ModeTraits<MODE>::kPerChunk);
   uint32_t mask = prefix_mask<MODE, KP>(b, p.athr_p[e], a, nq);
+  // Padding: rows past n carry +inf and positions past B start at -inf, but a
+  // float32 product that overflows is +inf itself and reaches both.
+  if (e >= p.n) mask = 0u;
+  if (qwave + kPrWaveQ > p.B) {
+    for (uint32_t m = mask; m != 0u; m &= m - 1u) {
+      const int bit = __builtin_ctz(m);
+      if (qwave + mask_row<32>(bit, lane) >= p.B) mask &= ~(1u << bit);
+    }
+  }
   if (mask != 0u) {
     int slot = atomicAdd(&pq.n, __builtin_popcount(mask));
     for (; mask != 0u && slot < kPrQueue; mask &= mask - 1u, ++slot) {
@@ -1696,7 +1705,10 @@ __global__ __launch_bounds__(256) void recheck_prefix_kernel(const RecheckArgs p
   for (int64_t b = w * 16; b < total; b += waves * 16) {
     // pair b + m16, the last pair again past the end
     const int64_t i = b + m16 < total ? b + m16 : total - 1;
-    const int64_t q = gpos[i], e = ge[i];
+    // padded pairs (products that overflow, see prefix_survivor) are dropped
+    const int64_t qi = gpos[i], ei = ge[i];
+    const bool live = qi < p.qend && ei < p.n;
+    const int64_t q = live ? qi : 0, e = live ? ei : 0;
     const float qq = qthr[q], an = athr[e];
     f32x4 qrow;
 #pragma unroll
@@ -1714,7 +1726,7 @@ __global__ __launch_bounds__(256) void recheck_prefix_kernel(const RecheckArgs p
     float v = acc[0];
 #pragma unroll
     for (int r = 1; r < 4; ++r) v = (m16 & 3) == r ? acc[r] : v;
-    const bool pass = (FOLD ? v : v - qq) >= an;
+    const bool pass = live && (FOLD ? v : v - qq) >= an;
     unsigned long long keep = __ballot(pass && g == (m16 >> 2) && b + m16 < total);
     while (keep != 0ull) {
       // the next four: lane j < 4 takes the j-th set lane's pair
@@ -2219,8 +2231,9 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
   if (prune && launch_dense(precision, view->store_dtype, pl, p, s) != hipSuccess) return LIPCACHE_EHIP;
   if (dump) return LIPCACHE_OK;
   // the pairs the scan's waves queued, one chip-wide pass
-  const RecheckArgs ra{zq, view->z, view->r, best, bflag, stats, static_cast<int64_t>(LLONG_MAX), view->n, view->d,
-                       emap, eoff, qlist, false};
+  // (positions of a work list index qlist; a wave only queues those of its item)
+  const RecheckArgs ra{zq, view->z, view->r, best, bflag, stats, items ? static_cast<int64_t>(LLONG_MAX) : B, view->n,
+                       view->d, emap, eoff, qlist, false};
   int64_t blocks = (gq_cap + 15) / 16;
   if (blocks > 512) blocks = 512;
   if (prune) {

@@ -4,8 +4,6 @@ The matrix tiles are padded: query positions past the batch (or past a
 cluster's list) start at -inf, rows past n carry a threshold of +inf.  Every
 count below is exact, so one padded pair let through shows in it.
 """
-import ctypes
-
 import numpy as np
 import pytest
 import torch
@@ -61,3 +59,36 @@ def test_unbounded_radius(path, n, d):
     st = host(res.stats)
     assert st[L.STAT_HITS] == 3 and st[L.STAT_RECHECKED] == 9, st.tolist()
     assert st[L.STAT_BAND_PAIRS] == 3 and st[L.STAT_BAND_QUERIES] == 3, st.tolist()
+
+
+@pytest.mark.parametrize("n,d,B", [(70001, 96, 5), (40003, 128, 600)])
+def test_overflowing_products(n, d, B):
+    """Finite features past the documented range (products of +inf in the
+    float32 filter), the last live row among them: it stands in for the rows
+    past n of the last tile.  The spare rows of the cache hold balls around
+    everything, so a row past n that is read would be a hit."""
+    say("overflowing products", n, d, B)
+    assert (B + 511) // 512 * 512 * n * (d - 32) >= 2**30  # takes the prefix scan
+    rng = np.random.default_rng(n)
+    spare = 1200
+    c = api.LipCache(d, n + spare, device="cuda:0", image=False)
+    z = rng.standard_normal((n + spare, d)).astype(np.float32)
+    z[n - 3:n] = 1.0e18
+    r = np.full(n + spare, 0.5, np.float32)
+    r[n:] = 1.0e30
+    assert c.insert(gpu(z), gpu(np.zeros(n + spare, np.int32)), gpu(r)) == n + spare
+    c.n = n
+    zq = z[:B] + np.float32(0.001)
+    zq[2] = 3.0e20   # q . z overflows against the last rows only
+    zq[B - 1] = 3.0e20
+    keep = torch.zeros((B + 600, d), device="cuda:0")   # the batch inside a larger allocation
+    keep[:B] = gpu(zq)
+    q = keep[:B]
+    res = c.lookup(q, precision="f32")
+    full = full_contraction(c, q, L.F32)
+    want = np.arange(B)
+    want[[2, B - 1]] = -1
+    for what, o in (("prefix", res), ("full", full)):
+        assert host(o.index).tolist() == want.tolist(), what
+        st = host(o.stats)
+        assert st[L.STAT_HITS] == B - 2 and st[L.STAT_BAND_PAIRS] == 0, (what, st.tolist())
