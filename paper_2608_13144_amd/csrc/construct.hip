@@ -230,7 +230,7 @@ __global__ void construct_gather_kernel(const float* __restrict__ z, const int32
     src_c[j] = src;
     if (qthr) {
       qthr[j] = query_threshold(s, th);
-      athr[j] = entry_threshold(r[src], static_cast<float>(s), th.kappa_c, th.eta1, th.range2);
+      athr[j] = entry_threshold(r[src], s, th.kappa_c, th.eta1, th.range2);  // s: it may pass the float32 range
     }
   }
 }

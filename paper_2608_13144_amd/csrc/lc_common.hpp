@@ -280,10 +280,10 @@ __device__ __forceinline__ float entry_round_down(double x) {
   return f < kPassAll ? kPassAll : f;
 }
 
-// +inf for rows that can never be hit (r_i <= 0 or NaN).
-__device__ __forceinline__ float entry_threshold(float rr, float n2f, double kappa_c, double eta1, double range2) {
+// +inf for rows that can never be hit (r_i <= 0 or NaN).  n2 is ||z_i||^2, in
+// float64 or rounded to float32 (the 4u in kappa_c).
+__device__ __forceinline__ float entry_threshold(float rr, double n2, double kappa_c, double eta1, double range2) {
   if (!(rr > 0.0f)) return __builtin_inff();
-  const double n2 = static_cast<double>(n2f);
   if (n2 >= range2 && n2 < __builtin_inf()) return kPassAll;
   const double r2 = static_cast<double>(rr) * static_cast<double>(rr);
   return entry_round_down((kappa_c * n2 - r2) * 0.5 - eta1 * __builtin_sqrt(n2) - 0.5 * kFilterAbsSlack);

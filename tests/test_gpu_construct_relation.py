@@ -27,3 +27,16 @@ def test_dedup_relation(n, d, spread, scale, store):
     z[n // 2:] += 0.2 * rng.standard_normal((n - n // 2, d))
     r = scale * rng.uniform(0.05, 0.4, n)
     run_both((scale * z).astype(np.float32), rng.integers(0, 5, n).astype(np.int32), r.astype(np.float32), d, store=store)
+
+
+# 1e19 and 1e20: finite features whose squared norm passes the float32 range
+@pytest.mark.parametrize("scale", [1.0e18, 1.0e19, 1.0e20])
+def test_dedup_norms_past_float32(scale):
+    """Near copies within one chunk are duplicates at any finite magnitude."""
+    say("dedup norms past float32", scale)
+    rng = np.random.default_rng(19)
+    n, d = 700, 64
+    z = rng.standard_normal((7, d))[rng.integers(0, 7, n)] + 0.12 / np.sqrt(d) * rng.standard_normal((n, d))
+    r = (scale * rng.uniform(0.05, 0.4, n)).astype(np.float32)
+    _, _, sel = run_both((scale * z).astype(np.float32), rng.integers(0, 5, n).astype(np.int32), r, d)
+    assert sel.size < n // 4
