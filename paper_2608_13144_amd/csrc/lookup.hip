@@ -97,11 +97,16 @@ struct LookupParams {
   const float* athr_p;
   // Slices the prefix scan hands to the full contraction: one list per XCD
   // of (first query, slice, row to resume at), dn_cap slots each, dn_count
-  // entries reserved; pf_qblock is the prefix scan's query block.
+  // entries reserved; pf_qblock is the prefix scan's query block.  Slices
+  // whose pairs found the queue full: one list of (first query, first and
+  // last + 1 row), rs_count entries.
   int64_t* dn_work;
   int64_t* dn_row;
   unsigned long long* dn_count;
   int64_t dn_cap;
+  int64_t* rs_query;
+  int64_t* rs_rows;
+  unsigned long long* rs_count;
   int pf_qblock;
   int pf_limit;  // pairs that may pass per wave of queries and kPrRows rows
   const void* cimg;      // rows streamed by the DMA kernel (float16 image or z)
@@ -132,7 +137,6 @@ struct LookupParams {
   int64_t* gq_e;
   unsigned long long* gq_count;
   int64_t gq_cap;
-  bool near_only;        // see RecheckArgs
 };
 
 // ------------------------------------------------------------- prep
@@ -253,7 +257,7 @@ __global__ void lookup_prep_kernel(const float* __restrict__ zq, int64_t B, int 
   const int64_t q = static_cast<int64_t>(blockIdx.x) * kLkWaves + threadIdx.x / kWave;
   if (blockIdx.x == 0 && threadIdx.x < 4) stats[threadIdx.x] = 0;
   if (blockIdx.x == 0 && threadIdx.x == 4 && pe.gq_count) *pe.gq_count = 0ull;
-  if (blockIdx.x == 0 && threadIdx.x < kXcds && pe.dn_count) pe.dn_count[threadIdx.x] = 0ull;
+  if (blockIdx.x == 0 && threadIdx.x <= kXcds && pe.dn_count) pe.dn_count[threadIdx.x] = 0ull;
   if (q >= B) return;
   const float* row = zq + q * d;
   double s = 0.0, sp = 0.0;
@@ -455,18 +459,10 @@ struct RecheckArgs {
   const int64_t* emap;
   int64_t eoff;
   const int32_t* qlist;
-  // Prefix scan, pairs that find the queue full: count as re-checked only
-  // those that prove to lie in the widened ball (the full filter passes every
-  // one of them, so the count stays at most the full contraction's).
-  bool near_only;
 };
 
 __device__ __forceinline__ RecheckArgs recheck_args(const LookupParams& p, int64_t qend, const int32_t* qlist) {
-  return RecheckArgs{p.zq, p.cz, p.cr, p.best, p.bflag, p.stats, qend, p.n, p.d, p.emap, p.eoff, qlist, p.near_only};
-}
-
-__device__ __forceinline__ bool counts(bool near_only, double d2, double r) {
-  return !near_only || d2 <= r * r * (1.0 + kPrefixBand);
+  return RecheckArgs{p.zq, p.cz, p.cr, p.best, p.bflag, p.stats, qend, p.n, p.d, p.emap, p.eoff, qlist};
 }
 
 // ||q - z_e||^2 of query row q and cache row e in float64 over the whole
@@ -487,7 +483,7 @@ __device__ __forceinline__ double wave_dist2(const RecheckArgs& p, int64_t q, in
 // packed (d^2, entry) key of a hit into the query's minimum.
 __device__ __forceinline__ void record_pair(const RecheckArgs& p, int64_t q, int64_t e, double d2) {
   const double r = static_cast<double>(p.cr[e]);
-  if (counts(p.near_only, d2, r)) atomicAdd(&p.stats[LIPCACHE_STAT_RECHECKED], 1ull);
+  atomicAdd(&p.stats[LIPCACHE_STAT_RECHECKED], 1ull);
   const bool hit = d2 < r * r;
   if (__builtin_fabs(__builtin_sqrt(d2) - r) <= 1e-5 * r) {
     atomicAdd(&p.stats[LIPCACHE_STAT_BAND_PAIRS], 1ull);
@@ -516,7 +512,7 @@ __device__ __forceinline__ int mask_col(int lane) { return lane & (TILE - 1); }
 
 // Exact re-check of the pairs whose bits are set in `mask` (see mask_row),
 // one pair at a time by the whole wave.
-template <int SRC, int TILE = 16>
+template <int SRC>
 __device__ __noinline__ void recheck_pairs(const RecheckArgs p, uint32_t mask, int64_t qwave, int64_t ebase) {
   const int lane = lane_id();
   while (true) {
@@ -526,8 +522,8 @@ __device__ __noinline__ void recheck_pairs(const RecheckArgs p, uint32_t mask, i
     const uint32_t msrc = static_cast<uint32_t>(__shfl(static_cast<int>(mask), src, kWave));
     const int bit = __builtin_ctz(msrc);
     if (lane == src) mask &= mask - 1u;
-    const int64_t qpos = qwave + mask_row<TILE>(bit, src);
-    const int64_t e = ebase + mask_col<TILE>(src);
+    const int64_t qpos = qwave + mask_row<16>(bit, src);
+    const int64_t e = ebase + mask_col<16>(src);
     if (qpos >= p.qend || e >= p.n) continue;  // padded rows never pass; kept as a guard
     const int64_t q = query_at(p.qlist, qpos);
     const double d2 = wave_dist2<SRC>(p, q, e);
@@ -597,7 +593,6 @@ __device__ __forceinline__ int settle_four(const RecheckArgs& p, bool valid, int
       acc[j] = __builtin_fma(diff, diff, acc[j]);
     }
   }
-  bool counted = false;
 #pragma unroll
   for (int j = 0; j < P; ++j) {
     const double d2 = wave_sum(acc[j]);
@@ -605,7 +600,6 @@ __device__ __forceinline__ int settle_four(const RecheckArgs& p, bool valid, int
       // record_pair with the radius and key fetched above (the re-check
       // count is the caller's)
       const double r = static_cast<double>(mr);
-      counted = counts(p.near_only, d2, r);
       if (__builtin_fabs(__builtin_sqrt(d2) - r) <= 1e-5 * r) {
         atomicAdd(&p.stats[LIPCACHE_STAT_BAND_PAIRS], 1ull);
         atomicOr(&p.bflag[mq], 1u);
@@ -618,7 +612,7 @@ __device__ __forceinline__ int settle_four(const RecheckArgs& p, bool valid, int
       }
     }
   }
-  return __popcll(__ballot(counted));
+  return __popcll(__ballot(mq >= 0));
 }
 
 template <int SRC>
@@ -673,7 +667,7 @@ __device__ __forceinline__ uint64_t lane0_u64(uint64_t v) {
 // re-check queue, one pair per lane and pass with one reservation per pass.
 // Pairs that find no slot below the capacity are re-checked at once (a cold
 // path: the queue holds several pairs per query).
-template <int SRC, int TILE = 16>
+template <int SRC>
 __device__ __forceinline__ void enqueue_pairs(const LookupParams& lp, uint32_t mask, int64_t qwave, int64_t ebase,
                                               int64_t qend, const int32_t* qlist) {
   const int lane = lane_id();
@@ -691,15 +685,15 @@ __device__ __forceinline__ void enqueue_pairs(const LookupParams& lp, uint32_t m
       const uint64_t slot = base + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(bal >> 32),
                                                              __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u));
       if (slot < cap) {
-        lp.gq_pos[slot] = qwave + mask_row<TILE>(bit, lane);
-        lp.gq_e[slot] = ebase + mask_col<TILE>(lane);
+        lp.gq_pos[slot] = qwave + mask_row<16>(bit, lane);
+        lp.gq_e[slot] = ebase + mask_col<16>(lane);
       } else {
         rest |= 1u << bit;
       }
       mask &= mask - 1u;
     }
   }
-  if (__ballot(rest != 0u) != 0ull) recheck_pairs<SRC, TILE>(recheck_args(lp, qend, qlist), rest, qwave, ebase);
+  if (__ballot(rest != 0u) != 0ull) recheck_pairs<SRC>(recheck_args(lp, qend, qlist), rest, qwave, ebase);
 }
 
 // Work-list mode: moves the wave's LDS queue to the global queue when it
@@ -1365,9 +1359,15 @@ __global__ __launch_bounds__(NW * kWave, 2) void lookup_dma_kernel(const LookupP
 // data) the re-checks would cost more than the full contraction: about 0.7 ns
 // a pair over the whole chip, against 0.33 ps a contracted pair at d = 256.  So
 // the workgroup counts the pairs that pass, and past half of the full
-// contraction's time (pf_limit) it stops before settling the tile it is in and
-// puts the rest of its slice on a list, which the full kernel (same queue)
-// works off right after.
+// contraction's time (pf_limit) it stops before queueing those of the tile
+// before and puts the rest of its slice on a list, which the full kernel (same
+// queue) works off right after.
+//
+// The count also reserves the pairs' slots, a whole tile's at once.  A tile
+// that finds the global queue full is put on a second list, with those that
+// follow in its slice (they are still counted): the queue's re-check forms
+// their pairs again and settles them as the queued ones, so no answer and no
+// counter depends on which pairs found room.
 constexpr int kPrRows = 1024;               // slices are multiples of this; rows per tile of one step
 constexpr int kPrCol = 32;                  // rows per column tile
 constexpr int pr_rows(int kp) { return kPrRows / kp; }          // rows per prefix tile
@@ -1457,14 +1457,30 @@ __device__ __forceinline__ void prefix_operand(const unsigned char* buf, int sub
     b[kp] = *reinterpret_cast<const u32x4*>(buf + (sub * KP + kp) * (kPrCol * 32) + lane * 16);
 }
 
-// Pairs that pass in the surviving column tiles `pass` of the LDS tile (all
-// lanes).  In float16 a wave with more than half of its column tiles surviving
-// is not counted out (the full contraction costs little more than counting); in
-// float32 it is (the full contraction is d / 16 scans).
+// Padding: rows past n carry +inf and positions past B start at -inf, but a
+// float32 product that overflows is +inf itself and reaches both.
+__device__ __forceinline__ uint32_t prefix_live(const LookupParams& p, uint32_t mask, int64_t e, int64_t qwave) {
+  if (e >= p.n) mask = 0u;
+  if (qwave + kPrWaveQ > p.B) {
+    const int lane = lane_id();
+    for (uint32_t m = mask; m != 0u; m &= m - 1u) {
+      const int bit = __builtin_ctz(m);
+      if (qwave + mask_row<32>(bit, lane) >= p.B) mask &= ~(1u << bit);
+    }
+  }
+  return mask;
+}
+
+// Pairs that pass in the surviving column tiles `pass` of the LDS tile at row
+// t0 (all lanes).  In float16 a wave with more than half of its column tiles
+// surviving is not counted out (the full contraction costs little more than
+// counting); in float32 it is (the full contraction is d / 16 scans).
+constexpr int kPrTooMany = 1 << 27;  // past any limit; eight waves' stay within an int
 template <int MODE, int KP>
-__device__ __forceinline__ int prefix_count(const unsigned char* buf, const float* athp_buf, uint32_t pass,
-                                            const u32x4 (&a)[kPrRT][KP], const f32x16 (&nq)[kPrRT]) {
-  if (MODE == kModeF16 && __builtin_popcount(pass) > pr_subs(KP) / 2) return 1 << 20;
+__device__ __forceinline__ int prefix_count(const LookupParams& p, const unsigned char* buf, const float* athp_buf,
+                                            int64_t t0, int64_t qwave, uint32_t pass, const u32x4 (&a)[kPrRT][KP],
+                                            const f32x16 (&nq)[kPrRT]) {
+  if (MODE == kModeF16 && __builtin_popcount(pass) > pr_subs(KP) / 2) return kPrTooMany;
   const int lane = lane_id();
   int n = 0;
 #pragma unroll 1
@@ -1472,7 +1488,8 @@ __device__ __forceinline__ int prefix_count(const unsigned char* buf, const floa
     const int sub = __builtin_ctz(m);
     u32x4 b[KP];
     prefix_operand<KP>(buf, sub, lane, b);
-    n += __builtin_popcount(prefix_mask<MODE, KP>(b, athp_buf[sub * kPrCol + (lane & 31)], a, nq));
+    const uint32_t mask = prefix_mask<MODE, KP>(b, athp_buf[sub * kPrCol + (lane & 31)], a, nq);
+    n += __builtin_popcount(prefix_live(p, mask, t0 + sub * kPrCol + (lane & 31), qwave));
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o, kWave);
@@ -1485,16 +1502,65 @@ __device__ __forceinline__ int prefix_count(const unsigned char* buf, const floa
 constexpr int kPrQueue = 512;
 struct PrefixQueue {
   int32_t q[kPrQueue];  // query, relative to the workgroup's first
-  int32_t n;            // pairs offered (those past kPrQueue went straight to the global queue)
+  int32_t n;            // pairs placed so far, here or in the global queue
   int64_t e[kPrQueue];  // cache row
   int64_t base;
 };
+static_assert(kPrQueue <= kPrThreads, "one pair per thread");
 
-// A surviving column tile, rows [ebase, ebase + 32): its pairs found again
-// (the LDS tile may be gone) and queued.
-template <int MODE, int STORE, int KP>
-__device__ __forceinline__ void prefix_survivor(const LookupParams& p, int64_t ebase, int64_t q0, int64_t qwave,
-                                                const u32x4 (&a)[kPrRT][KP], const f32x16 (&nq)[kPrRT], PrefixQueue& pq) {
+// The first of `n` reserved slots of the global queue, or -1 where it has no
+// room for them all (the slots that exist are marked empty).  All waves, n
+// uniform; starts and ends with a barrier.
+__device__ __forceinline__ int64_t prefix_reserve(const LookupParams& p, int n, PrefixQueue& pq) {
+  __syncthreads();
+  if (threadIdx.x == 0) pq.base = static_cast<int64_t>(atomicAdd(p.gq_count, static_cast<unsigned long long>(n)));
+  __syncthreads();
+  const int64_t base = static_cast<int64_t>(lane0_u64(static_cast<uint64_t>(pq.base)));
+  if (base + n <= p.gq_cap) return base;
+  for (int64_t i = base + threadIdx.x; i < p.gq_cap; i += kPrThreads) p.gq_pos[i] = -1;
+  return -1;
+}
+
+// The workgroup's `n` queued pairs to slots base .. of the global queue.
+__device__ __forceinline__ void prefix_move(const LookupParams& p, int64_t base, int n, int64_t q0,
+                                            const PrefixQueue& pq) {
+  const int i = static_cast<int>(threadIdx.x);
+  if (i < n) {
+    p.gq_pos[base + i] = q0 + pq.q[i];
+    p.gq_e[base + i] = pq.e[i];
+  }
+}
+
+// A wave's queries as operands and start values (-Q'_q; positions past B never
+// pass).
+template <int MODE, int KP>
+__device__ __forceinline__ void prefix_queries(const LookupParams& p, int64_t qwave, u32x4 (&a)[kPrRT][KP],
+                                               f32x16 (&nq)[kPrRT]) {
+  const int lane = lane_id();
+#pragma unroll
+  for (int rt = 0; rt < kPrRT; ++rt) {
+    const int64_t q = qwave + rt * 32 + (lane & 31);
+#pragma unroll
+    for (int kp = 0; kp < KP; ++kp)
+      a[rt][kp] = load_chunk<MODE, LIPCACHE_F32>(p.zq, q < p.B ? q : p.B - 1, p.d,
+                                                 (2 * kp + (lane >> 5)) * ModeTraits<MODE>::kPerChunk);
+    // four consecutive queries per group (the array is padded to 64)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t qi = qwave + mask_row<32>(rt * 16 + 4 * j, lane);
+      f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (qwave < p.B) t = *reinterpret_cast<const f32x4*>(p.qthr_p + qi);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) nq[rt][4 * j + i] = qi + i < p.B ? -t[i] : -__builtin_inff();
+    }
+  }
+}
+
+// The pairs that pass in the column tile of rows [ebase, ebase + 32), formed
+// from global memory (the LDS tile may be gone).
+template <int MODE, int KP>
+__device__ __forceinline__ uint32_t prefix_found(const LookupParams& p, int64_t ebase, int64_t qwave,
+                                                 const u32x4 (&a)[kPrRT][KP], const f32x16 (&nq)[kPrRT]) {
   const int lane = lane_id();
   const int64_t e = ebase + (lane & 31);
   u32x4 b[KP];
@@ -1502,46 +1568,31 @@ __device__ __forceinline__ void prefix_survivor(const LookupParams& p, int64_t e
   for (int kp = 0; kp < KP; ++kp)
     b[kp] = load_chunk<MODE, MODE == kModeF16 ? LIPCACHE_F16 : LIPCACHE_F32>(
         p.cimg, e < p.n ? e : p.n - 1, p.d, (2 * kp + (lane >> 5)) * ModeTraits<MODE>::kPerChunk);
-  uint32_t mask = prefix_mask<MODE, KP>(b, p.athr_p[e], a, nq);
-  // Padding: rows past n carry +inf and positions past B start at -inf, but a
-  // float32 product that overflows is +inf itself and reaches both.
-  if (e >= p.n) mask = 0u;
-  if (qwave + kPrWaveQ > p.B) {
-    for (uint32_t m = mask; m != 0u; m &= m - 1u) {
-      const int bit = __builtin_ctz(m);
-      if (qwave + mask_row<32>(bit, lane) >= p.B) mask &= ~(1u << bit);
-    }
-  }
-  if (mask != 0u) {
-    int slot = atomicAdd(&pq.n, __builtin_popcount(mask));
-    for (; mask != 0u && slot < kPrQueue; mask &= mask - 1u, ++slot) {
-      pq.q[slot] = static_cast<int32_t>(qwave - q0) + mask_row<32>(__builtin_ctz(mask), lane);
-      pq.e[slot] = e;
-    }
-  }
-  if (__ballot(mask != 0u) != 0ull) enqueue_pairs<STORE, 32>(p, mask, qwave, ebase, p.B, nullptr);
+  return prefix_live(p, prefix_mask<MODE, KP>(b, p.athr_p[e], a, nq), e, qwave);
 }
 
-// The workgroup's queue to the global one (all waves; the queue is complete).
-template <int STORE>
-__device__ __forceinline__ void prefix_flush(const LookupParams& p, int64_t q0, PrefixQueue& pq) {
-  const int n = pq.n < kPrQueue ? pq.n : kPrQueue;
-  if (n == 0) return;
-  if (threadIdx.x == 0) pq.base = static_cast<int64_t>(atomicAdd(p.gq_count, static_cast<unsigned long long>(n)));
-  __syncthreads();
-  const int64_t base = pq.base;
-  const int64_t left = p.gq_cap - base;
-  const int room = left <= 0 ? 0 : left < n ? static_cast<int>(left) : n;
-  const int i = static_cast<int>(threadIdx.x);
-  if (i < room) {
-    p.gq_pos[base + i] = q0 + pq.q[i];
-    p.gq_e[base + i] = pq.e[i];
+// Places the pairs of a surviving column tile: slots of the workgroup's queue,
+// or with direct >= 0 the global ones from there on.  `placed`: pq.n at the
+// first of them, `room`: how many there are (the count's, so all fit).
+template <int MODE, int KP>
+__device__ __forceinline__ void prefix_survivor(const LookupParams& p, int64_t ebase, int64_t q0, int64_t qwave,
+                                                const u32x4 (&a)[kPrRT][KP], const f32x16 (&nq)[kPrRT], PrefixQueue& pq,
+                                                int64_t direct, int placed, int room) {
+  const int lane = lane_id();
+  uint32_t mask = prefix_found<MODE, KP>(p, ebase, qwave, a, nq);
+  if (mask == 0u) return;
+  int slot = atomicAdd(&pq.n, __builtin_popcount(mask)) - placed;
+  for (; mask != 0u && slot < room; mask &= mask - 1u, ++slot) {
+    const int row = mask_row<32>(__builtin_ctz(mask), lane);
+    if (direct >= 0) {
+      p.gq_pos[direct + slot] = qwave + row;
+      p.gq_e[direct + slot] = ebase + mask_col<32>(lane);
+    } else {
+      pq.q[slot] = static_cast<int32_t>(qwave - q0) + row;
+      pq.e[slot] = ebase + mask_col<32>(lane);
+    }
   }
-  // no room in the global queue: settled here
-  if (room < n && threadIdx.x < kWave)
-    settle_queue<STORE>(recheck_args(p, p.B, nullptr), pq.q + room, pq.e + room, n - room, q0);
 }
-static_assert(kPrQueue <= kPrThreads, "one pair per thread");
 
 // Column tiles ew, ew + EW, ... of one prefix tile against the wave's 64
 // queries; returns the wave-uniform mask of those where a pair passes.
@@ -1585,7 +1636,7 @@ __device__ __forceinline__ uint32_t prefix_tile(const unsigned char* buf, const 
   return pass << ew;
 }
 
-template <int MODE, int STORE, int KP, int EW>
+template <int MODE, int KP, int EW>
 __global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const LookupParams p) {
   // the thresholds first: their reads then fit the LDS instruction's offset
   struct Tiles {
@@ -1616,137 +1667,223 @@ __global__ __launch_bounds__(kPrThreads, 4) void lookup_prefix_kernel(const Look
 
   u32x4 a[kPrRT][KP];
   f32x16 nq[kPrRT];
-#pragma unroll
-  for (int rt = 0; rt < kPrRT; ++rt) {
-    const int64_t q = qwave + rt * 32 + (lane & 31);
-#pragma unroll
-    for (int kp = 0; kp < KP; ++kp)
-      a[rt][kp] = load_chunk<MODE, LIPCACHE_F32>(p.zq, q < p.B ? q : p.B - 1, p.d,
-                                                 (2 * kp + (lane >> 5)) * ModeTraits<MODE>::kPerChunk);
-    // four consecutive queries per group (the array is padded to 64)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t qi = qwave + mask_row<32>(rt * 16 + 4 * j, lane);
-      f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (active) t = *reinterpret_cast<const f32x4*>(p.qthr_p + qi);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) nq[rt][4 * j + i] = qi + i < p.B ? -t[i] : -__builtin_inff();
-    }
-  }
+  prefix_queries<MODE, KP>(p, qwave, a, nq);
 
   int seen[2] = {0, 0};
   int total = 0, allowed = limit;
   bool stopped = false;
   uint32_t pass = 0u;
+  // pairs placed before the workgroup's queue was last emptied, pairs in it,
+  // and the tile of its first
+  int placed = 0, queued = 0;
+  int64_t queue_row = e_begin;
+  int64_t full_row = -1;  // from this tile on the queue was full
   int64_t t0 = e_begin;
   for (int cur = 0;; cur ^= 1, t0 += kRows) {
     wait_copies();
     __syncthreads();  // publishes tile t0 and the count of the tile before
+    int64_t direct = -1;
+    int need = 0;  // pairs of the tile before
     if (t0 > e_begin) {
       // Each slot only grows and is next added to after the following
       // barrier, so every wave reads the same count and takes the same turn.
       const int now = uniform(passed[cur ^ 1]);
-      total += now - seen[cur ^ 1];
+      need = now - seen[cur ^ 1];
+      total += need;
       seen[cur ^ 1] = now;
-      allowed += limit;
+      allowed = allowed + limit < kPrTooMany ? allowed + limit : kPrTooMany - 1;
       if (total > allowed) {
         stopped = true;
         break;
       }
+      if (full_row < 0 && need > 0) {
+        if (queued == 0) queue_row = t0 - kRows;
+        if (queued + need > kPrQueue) {
+          // the queue so far, and the tile itself where it alone is too much
+          const bool alone = need > kPrQueue;
+          const int64_t base = prefix_reserve(p, queued + (alone ? need : 0), sh.pq);
+          if (base >= 0) {
+            prefix_move(p, base, queued, q0, sh.pq);
+            __syncthreads();  // before the queue is written again
+            if (alone) direct = base + queued;
+            placed += queued;
+            queue_row = t0 - kRows;
+          } else {
+            full_row = queue_row;
+          }
+          queued = 0;
+        }
+      }
     }
     const bool more = t0 + kRows < e_end;
     if (more) issue_prefix_tile<MODE, KP>(buf[cur ^ 1], athp[cur ^ 1], p, t0 + kRows, wave);
-    // settle the tile before while this tile's operands are in LDS
-    for (uint32_t m = pass; m != 0u; m &= m - 1u)
-      prefix_survivor<MODE, STORE, KP>(p, t0 - kRows + __builtin_ctz(m) * kPrCol, q0, qwave, a, nq, sh.pq);
+    // place the pairs of the tile before while this tile's operands are in LDS
+    if (full_row < 0) {
+      for (uint32_t m = pass; m != 0u; m &= m - 1u)
+        prefix_survivor<MODE, KP>(p, t0 - kRows + __builtin_ctz(m) * kPrCol, q0, qwave, a, nq, sh.pq, direct, placed,
+                                  direct >= 0 ? need : kPrQueue);
+      if (direct >= 0) {
+        placed += need;
+      } else {
+        queued += need;
+      }
+    }
     if (t0 >= e_end) break;
     pass = active ? prefix_tile<MODE, KP, EW>(buf[cur], athp[cur], ew, a, nq) : 0u;
     if (pass != 0u) {
-      const int n = prefix_count<MODE, KP>(buf[cur], athp[cur], pass, a, nq);
+      const int n = prefix_count<MODE, KP>(p, buf[cur], athp[cur], t0, qwave, pass, a, nq);
       if (lane == 0) atomicAdd(&passed[cur], n);
     }
   }
-  __syncthreads();  // the queue is complete
-  prefix_flush<STORE>(p, q0, sh.pq);
-  // The tile before t0 and the rest of the slice go to the full contraction.
-  if (stopped && threadIdx.x == 0) {
+  if (full_row < 0 && queued > 0) {
+    const int64_t base = prefix_reserve(p, queued, sh.pq);
+    if (base >= 0) {
+      prefix_move(p, base, queued, q0, sh.pq);
+    } else {
+      full_row = queue_row;
+    }
+  }
+  if (threadIdx.x != 0) return;
+  // stopped: the tile before t0 and the rest of the slice go to the full contraction
+  const int64_t done = stopped ? t0 - kRows : e_end;
+  if (stopped) {
     const int xcd = static_cast<int>(blockIdx.x) % kXcds;
     const int64_t slot = static_cast<int64_t>(atomicAdd(&p.dn_count[xcd], 1ull)) + xcd * p.dn_cap;
     p.dn_work[slot] = q0 * (1ll << 24) + e_begin / p.slice_len;
-    p.dn_row[slot] = t0 - kRows;
+    p.dn_row[slot] = done;
+  }
+  if (full_row >= 0 && full_row < done) {
+    const int64_t slot = static_cast<int64_t>(atomicAdd(p.rs_count, 1ull));
+    p.rs_query[slot] = q0;
+    p.rs_rows[slot] = full_row / kPrCol * (1ll << 32) + (done + kPrCol - 1) / kPrCol;
   }
 }
 
-// The queue of a prefix scan: the full filter first (all d features, the full
-// kernel's own instructions in its order, so its own dot products),
-// then the exact re-check of the pairs it passes.  A wave takes 16 pairs:
-// pair i is row i and column i of one 16x16 block, its dot product the
-// block's diagonal.  The filter reads half the bytes of the float64 sum and
-// drops most pairs the 16 features could not (and the counter keeps its
-// meaning: pairs both filters let through).  FOLD as kFoldQ.
+// The full filter of pairs that passed a prefix scan: all d features, the full
+// kernel's own instructions in its order, so its own dot products; then the
+// exact re-check of those it passes.  The filter reads half the bytes of the
+// float64 sum and drops most pairs the prefix could not (and the counter
+// keeps its meaning: pairs both filters let through).  FOLD as kFoldQ.
+//
+// Up to 16 pairs: lane (m16, g) brings pair m16 in all four groups g; the pair
+// is row and column m16 of one 16x16 block, its dot product the block's
+// diagonal.  All 64 lanes call it; returns the number of pairs re-checked.
 template <int MODE, int SRC, bool FOLD>
-__global__ __launch_bounds__(256) void recheck_prefix_kernel(const RecheckArgs p, const void* __restrict__ cimg,
-                                                             const float* __restrict__ qthr,
-                                                             const float* __restrict__ athr,
-                                                             const int64_t* __restrict__ gpos,
-                                                             const int64_t* __restrict__ ge,
-                                                             const unsigned long long* __restrict__ gcount,
-                                                             int64_t cap) {
-  __shared__ unsigned int block_done;
+__device__ __forceinline__ int settle_filtered(const LookupParams& lp, const RecheckArgs& p, bool have, int64_t qi,
+                                               int64_t ei) {
   const int lane = lane_id();
   const int m16 = lane & 15, g = lane >> 4;
+  const bool live = have && qi >= 0 && qi < p.qend && ei < p.n;
+  const int64_t q = live ? qi : 0, e = live ? ei : 0;
+  const float qq = lp.qthr[q], an = lp.athr[e];
+  f32x4 qrow;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) qrow[r] = __shfl(qq, 4 * g + r, kWave);
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[r] = -qrow[r];
+  }
+#pragma unroll 4
+  for (int k0 = g * ModeTraits<MODE>::kPerChunk; k0 < p.d; k0 += ModeTraits<MODE>::kPerStep)
+    acc = mfma_step<MODE>(load_chunk<MODE, LIPCACHE_F32>(p.zq, q, p.d, k0),
+                          load_chunk<MODE, MODE == kModeF16 ? LIPCACHE_F16 : LIPCACHE_F32>(lp.cimg, e, p.d, k0), acc);
+  // lane (m16, g = m16 / 4) holds the diagonal element of pair m16
+  float v = acc[0];
+#pragma unroll
+  for (int r = 1; r < 4; ++r) v = (m16 & 3) == r ? acc[r] : v;
+  const bool pass = live && (FOLD ? v : v - qq) >= an;
+  unsigned long long keep = __ballot(pass && g == (m16 >> 2));
+  int done = 0;
+  while (keep != 0ull) {
+    // the next four: lane j < 4 takes the j-th set lane's pair
+    int src = 0;
+    bool mine = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (keep != 0ull) {
+        const int l = __builtin_ctzll(keep);
+        keep &= keep - 1ull;
+        if (lane == j) {
+          src = l;
+          mine = true;
+        }
+      }
+    }
+    const int64_t qs = __shfl(q, src, kWave), es = __shfl(e, src, kWave);
+    done += settle_four<SRC>(p, mine, mine ? qs : 0, mine ? es : 0);
+  }
+  return done;
+}
+
+// The pairs of the listed slices that found the queue full.  A wave takes one
+// of its workgroup's 64 queries and a run of 32 column tiles at a time, from
+// global memory (a cold path: the queue holds 4 B + 65,536 pairs).
+template <int MODE, int SRC, bool FOLD, int KP>
+__device__ __forceinline__ int settle_listed(const LookupParams& lp, int64_t wave, int64_t waves) {
+  const RecheckArgs p = recheck_args(lp, lp.B, nullptr);
+  const int lane = lane_id(), m16 = lane & 15;
+  const int64_t items = static_cast<int64_t>(*lp.rs_count);
+  const int64_t qw = lp.pf_qblock / kPrWaveQ;
+  int done = 0;
+  int64_t first = 0;  // units of the items before
+  for (int64_t item = 0; item < items; ++item) {
+    const int64_t begin = lp.rs_rows[item] >> 32, end = lp.rs_rows[item] & 0xffffffffll;  // column tiles
+    const int64_t units = qw * ((end - begin + 31) / 32);
+    // the wave's first unit of this item: first + u = wave (mod waves)
+    for (int64_t u = (wave - first % waves + waves) % waves; u < units; u += waves) {
+      const int64_t qwave = lp.rs_query[item] + u % qw * kPrWaveQ;
+      if (qwave >= lp.B) continue;
+      u32x4 a[kPrRT][KP];
+      f32x16 nq[kPrRT];
+      prefix_queries<MODE, KP>(lp, qwave, a, nq);
+      const int64_t c0 = begin + u / qw * 32, c1 = c0 + 32 < end ? c0 + 32 : end;
+      for (int64_t c = c0; c < c1; ++c) {
+        uint32_t mask = prefix_found<MODE, KP>(lp, c * kPrCol, qwave, a, nq);
+        while (true) {
+          // one pair of each of the first 16 lanes that hold any
+          unsigned long long bal = __ballot(mask != 0u);
+          if (bal == 0ull) break;
+          int src = -1;
+          for (int j = 0; j < 16 && bal != 0ull; ++j, bal &= bal - 1ull)
+            if (m16 == j) src = __builtin_ctzll(bal);
+          const int from = src < 0 ? 0 : src;
+          const uint32_t bits = static_cast<uint32_t>(__shfl(static_cast<int>(mask), from, kWave));
+          const int bit = __builtin_ctz(bits | 0x80000000u);
+          done += settle_filtered<MODE, SRC, FOLD>(lp, p, src >= 0, qwave + mask_row<32>(bit, from),
+                                                   c * kPrCol + mask_col<32>(from));
+          // bal: the lanes past the first 16
+          if (((bal >> lane) & 1ull) == 0ull) mask &= mask - 1u;
+        }
+      }
+    }
+    first += units;
+  }
+  return done;
+}
+
+// The queue of a prefix scan, 16 pairs a wave, and the listed slices.
+template <int MODE, int SRC, bool FOLD, int KP>
+__global__ __launch_bounds__(256, 2) void recheck_prefix_kernel(const LookupParams lp) {
+  __shared__ unsigned int block_done;
+  const int lane = lane_id();
+  const int m16 = lane & 15;
   if (threadIdx.x == 0) block_done = 0u;
   __syncthreads();
-  const int64_t reserved = static_cast<int64_t>(*gcount);
-  const int64_t total = reserved < cap ? reserved : cap;
+  const int64_t reserved = static_cast<int64_t>(*lp.gq_count);
+  const int64_t total = reserved < lp.gq_cap ? reserved : lp.gq_cap;
   const int64_t waves = static_cast<int64_t>(gridDim.x) * (blockDim.x / kWave);
   const int64_t w = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
+  const RecheckArgs p = recheck_args(lp, lp.B, nullptr);
   int done = 0;
   for (int64_t b = w * 16; b < total; b += waves * 16) {
     // pair b + m16, the last pair again past the end
-    const int64_t i = b + m16 < total ? b + m16 : total - 1;
-    // padded pairs (products that overflow, see prefix_survivor) are dropped
-    const int64_t qi = gpos[i], ei = ge[i];
-    const bool live = qi < p.qend && ei < p.n;
-    const int64_t q = live ? qi : 0, e = live ? ei : 0;
-    const float qq = qthr[q], an = athr[e];
-    f32x4 qrow;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) qrow[r] = __shfl(qq, 4 * g + r, kWave);
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (FOLD) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[r] = -qrow[r];
-    }
-#pragma unroll 4
-    for (int k0 = g * ModeTraits<MODE>::kPerChunk; k0 < p.d; k0 += ModeTraits<MODE>::kPerStep)
-      acc = mfma_step<MODE>(load_chunk<MODE, LIPCACHE_F32>(p.zq, q, p.d, k0),
-                            load_chunk<MODE, MODE == kModeF16 ? LIPCACHE_F16 : LIPCACHE_F32>(cimg, e, p.d, k0), acc);
-    // lane (m16, g = m16 / 4) holds the diagonal element of pair m16
-    float v = acc[0];
-#pragma unroll
-    for (int r = 1; r < 4; ++r) v = (m16 & 3) == r ? acc[r] : v;
-    const bool pass = live && (FOLD ? v : v - qq) >= an;
-    unsigned long long keep = __ballot(pass && g == (m16 >> 2) && b + m16 < total);
-    while (keep != 0ull) {
-      // the next four: lane j < 4 takes the j-th set lane's pair
-      int src = 0;
-      bool mine = false;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (keep != 0ull) {
-          const int l = __builtin_ctzll(keep);
-          keep &= keep - 1ull;
-          if (lane == j) {
-            src = l;
-            mine = true;
-          }
-        }
-      }
-      const int64_t qs = __shfl(q, src, kWave), es = __shfl(e, src, kWave);
-      done += settle_four<SRC>(p, mine, mine ? qs : 0, mine ? es : 0);
-    }
+    const bool have = b + m16 < total;
+    const int64_t i = have ? b + m16 : total - 1;
+    const int64_t qi = lp.gq_pos[i];
+    done += settle_filtered<MODE, SRC, FOLD>(lp, p, have, qi, qi >= 0 ? lp.gq_e[i] : 0);
   }
+  if (*lp.rs_count != 0ull) done += settle_listed<MODE, SRC, FOLD, KP>(lp, w, waves);
   if (lane == 0 && done) atomicAdd(&block_done, static_cast<unsigned int>(done));
   __syncthreads();
   if (threadIdx.x == 0 && block_done)
@@ -1842,12 +1979,12 @@ hipError_t launch_lookup(int precision, int store, const Plan& pl, const LookupP
 }
 
 // The prefix scan, EW waves of a workgroup on the same 64 queries (prefix_ew).
-template <int MODE, int STORE, int KP>
+template <int MODE, int KP>
 hipError_t launch_prefix_ew(int ew, const LookupParams& p, unsigned grid, hipStream_t s) {
   switch (ew) {
-#define LC_PCASE(E)                                                                                         \
-  case E:                                                                                                   \
-    hipLaunchKernelGGL((lookup_prefix_kernel<MODE, STORE, KP, E>), dim3(grid), dim3(kPrThreads), 0, s, p);  \
+#define LC_PCASE(E)                                                                                  \
+  case E:                                                                                            \
+    hipLaunchKernelGGL((lookup_prefix_kernel<MODE, KP, E>), dim3(grid), dim3(kPrThreads), 0, s, p);  \
     return hipGetLastError();
     LC_PCASE(1)
     LC_PCASE(2)
@@ -1859,42 +1996,30 @@ hipError_t launch_prefix_ew(int ew, const LookupParams& p, unsigned grid, hipStr
 }
 
 // The float32 filter scans only a float32 store, two steps (prune_consts).
-inline hipError_t launch_prefix(int precision, int store, int kp, int ew, const LookupParams& p, unsigned grid,
-                                hipStream_t s) {
-  if (precision == LIPCACHE_F32) return launch_prefix_ew<kModeF32, LIPCACHE_F32, 2>(ew, p, grid, s);
-  if (kp == 1)
-    return store == LIPCACHE_F32 ? launch_prefix_ew<kModeF16, LIPCACHE_F32, 1>(ew, p, grid, s)
-                                 : launch_prefix_ew<kModeF16, LIPCACHE_BF16, 1>(ew, p, grid, s);
-  return store == LIPCACHE_F32 ? launch_prefix_ew<kModeF16, LIPCACHE_F32, 2>(ew, p, grid, s)
-                               : launch_prefix_ew<kModeF16, LIPCACHE_BF16, 2>(ew, p, grid, s);
+inline hipError_t launch_prefix(int precision, int kp, int ew, const LookupParams& p, unsigned grid, hipStream_t s) {
+  if (precision == LIPCACHE_F32) return launch_prefix_ew<kModeF32, 2>(ew, p, grid, s);
+  return kp == 1 ? launch_prefix_ew<kModeF16, 1>(ew, p, grid, s) : launch_prefix_ew<kModeF16, 2>(ew, p, grid, s);
 }
 
-struct PrefixQueueArgs {
-  const void* cimg;
-  const float* qthr;
-  const float* athr;
-  const int64_t* gpos;
-  const int64_t* ge;
-  const unsigned long long* gcount;
-  int64_t cap;
-};
-
-template <int MODE, int STORE, bool FOLD>
-hipError_t launch_prefix_recheck_as(unsigned grid, hipStream_t s, const RecheckArgs& ra, const PrefixQueueArgs& q) {
-  hipLaunchKernelGGL((recheck_prefix_kernel<MODE, STORE, FOLD>), dim3(grid), dim3(256), 0, s, ra, q.cimg, q.qthr,
-                     q.athr, q.gpos, q.ge, q.gcount, q.cap);
+template <int MODE, int STORE, bool FOLD, int KP>
+hipError_t launch_prefix_recheck_as(unsigned grid, hipStream_t s, const LookupParams& p) {
+  hipLaunchKernelGGL((recheck_prefix_kernel<MODE, STORE, FOLD, KP>), dim3(grid), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
-inline hipError_t launch_prefix_recheck(int precision, int store, int ks, unsigned grid, hipStream_t s,
-                                        const RecheckArgs& ra, const PrefixQueueArgs& q) {
+template <int STORE>
+hipError_t launch_prefix_recheck_f16(int ks, int kp, unsigned grid, hipStream_t s, const LookupParams& p) {
+  if (kp == 1) return launch_prefix_recheck_as<kModeF16, STORE, false, 1>(grid, s, p);  // d >= 192
+  return ks <= 4 ? launch_prefix_recheck_as<kModeF16, STORE, true, 2>(grid, s, p)
+                 : launch_prefix_recheck_as<kModeF16, STORE, false, 2>(grid, s, p);
+}
+
+inline hipError_t launch_prefix_recheck(int precision, int store, int ks, int kp, unsigned grid, hipStream_t s,
+                                        const LookupParams& p) {
   static_assert(kFoldQ<kModeF16, 4> && !kFoldQ<kModeF16, 8> && !kFoldQ<kModeF32, 2>, "the full kernel's filter");
-  if (precision == LIPCACHE_F32) return launch_prefix_recheck_as<kModeF32, LIPCACHE_F32, false>(grid, s, ra, q);
-  if (store == LIPCACHE_F32)
-    return ks <= 4 ? launch_prefix_recheck_as<kModeF16, LIPCACHE_F32, true>(grid, s, ra, q)
-                   : launch_prefix_recheck_as<kModeF16, LIPCACHE_F32, false>(grid, s, ra, q);
-  return ks <= 4 ? launch_prefix_recheck_as<kModeF16, LIPCACHE_BF16, true>(grid, s, ra, q)
-                 : launch_prefix_recheck_as<kModeF16, LIPCACHE_BF16, false>(grid, s, ra, q);
+  if (precision == LIPCACHE_F32) return launch_prefix_recheck_as<kModeF32, LIPCACHE_F32, false, 2>(grid, s, p);
+  return store == LIPCACHE_F32 ? launch_prefix_recheck_f16<LIPCACHE_F32>(ks, kp, grid, s, p)
+                               : launch_prefix_recheck_f16<LIPCACHE_BF16>(ks, kp, grid, s, p);
 }
 
 // Waves that share 64 queries: the fewest query blocks the batch fills.
@@ -2167,6 +2292,9 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
   p.dn_row = nullptr;
   p.dn_count = nullptr;
   p.dn_cap = 0;
+  p.rs_query = nullptr;
+  p.rs_rows = nullptr;
+  p.rs_count = nullptr;
   p.pf_qblock = 0;
   p.pf_limit = 0;
   int64_t grid = n_items;
@@ -2193,12 +2321,16 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
     const int64_t slices = kXcds * s8;
     p.slice_len = ((tiles + slices - 1) / slices) * kPrRows;
     grid = slices * p.n_qblocks;
-    // the lists of slices for the full kernel take the queue's last slots
+    // the lists of slices, for the full kernel and of those that found the
+    // queue full, take the queue's last slots (one entry a workgroup in each)
     p.dn_cap = s8 * p.n_qblocks;
-    gq_cap -= grid;
+    gq_cap -= 2 * grid;
     p.dn_work = gq.pos + gq_cap;
     p.dn_row = gq.e + gq_cap;
     p.dn_count = gq.count + 1;
+    p.rs_query = p.dn_work + grid;
+    p.rs_rows = p.dn_row + grid;
+    p.rs_count = p.dn_count + kXcds;
   } else if (!items) {
     // Cache slices: a multiple of 8 (one set per XCD), enough blocks to fill
     // the chip (~kGridTarget), but at least 4 tiles per slice as long as that
@@ -2220,12 +2352,11 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
   }
   if (grid > INT_MAX || gq_cap < 0) return LIPCACHE_EUNSUPPORTED;
   p.gq_cap = gq_cap;
-  p.near_only = prune;
   const unsigned gu = static_cast<unsigned>(grid);
   const hipError_t e = dump    ? launch_lookup<kVarDump>(precision, view->store_dtype, pl, p, gu, s)
                        : items ? (pl.waves == kListWaves ? launch_lookup<kVarList>(precision, view->store_dtype, pl, p, gu, s)
                                                          : launch_lookup<kVarList8>(precision, view->store_dtype, pl, p, gu, s))
-                       : prune ? launch_prefix(precision, view->store_dtype, fc.pn.kp, ew, p, gu, s)
+                       : prune ? launch_prefix(precision, fc.pn.kp, ew, p, gu, s)
                                : launch_lookup<kVarLookup>(precision, view->store_dtype, pl, p, gu, s);
   if (e != hipSuccess) return LIPCACHE_EHIP;
   if (prune && launch_dense(precision, view->store_dtype, pl, p, s) != hipSuccess) return LIPCACHE_EHIP;
@@ -2233,13 +2364,12 @@ lipcache_status lookup_stage_scan(const lipcache_cache* view, int32_t precision,
   // the pairs the scan's waves queued, one chip-wide pass
   // (positions of a work list index qlist; a wave only queues those of its item)
   const RecheckArgs ra{zq, view->z, view->r, best, bflag, stats, items ? static_cast<int64_t>(LLONG_MAX) : B, view->n,
-                       view->d, emap, eoff, qlist, false};
+                       view->d, emap, eoff, qlist};
   int64_t blocks = (gq_cap + 15) / 16;
   if (blocks > 512) blocks = 512;
   if (prune) {
     const hipError_t er =
-        launch_prefix_recheck(precision, view->store_dtype, pl.ks, static_cast<unsigned>(blocks), s, ra,
-                              PrefixQueueArgs{p.cimg, qthr, athr, gq.pos, gq.e, gq.count, gq_cap});
+        launch_prefix_recheck(precision, view->store_dtype, pl.ks, fc.pn.kp, static_cast<unsigned>(blocks), s, p);
     return er == hipSuccess ? LIPCACHE_OK : LIPCACHE_EHIP;
   }
   if (view->store_dtype == LIPCACHE_BF16) {
