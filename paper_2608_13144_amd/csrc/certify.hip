@@ -326,13 +326,14 @@ __device__ __forceinline__ void stage_head(const float* __restrict__ W, int C, i
   }
 }
 
-// With `pending` a fixed grid looks every block of rows through for labels the
-// filter left (kCertPending), and forms and writes only those.
-template <bool BF16_STORE, bool TIGHT, int KQ>
+// PENDING: a fixed grid looks every block of rows through for labels the
+// filter left (kCertPending), and forms and writes only those; else a
+// workgroup has one block.
+template <bool BF16_STORE, bool TIGHT, int KQ, bool PENDING>
 __global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
     const float* __restrict__ z, int64_t N, int d, const float* __restrict__ W, const float* __restrict__ b, int C,
     double sigma, const double* __restrict__ row_dist, const double* __restrict__ dmax, int32_t* __restrict__ label_out,
-    float* __restrict__ r_out, float* __restrict__ margin_out, float* __restrict__ norm2_out, bool pending) {
+    float* __restrict__ r_out, float* __restrict__ margin_out, float* __restrict__ norm2_out) {
   extern __shared__ float wl[];  // kCmClasses rows of stride 16 KQ + 4 floats
   constexpr int kWidth = 16 * KQ;
   constexpr int stride = kWidth + 4;
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
   const int64_t blocks = (N + kCmRows - 1) / kCmRows;
   for (int64_t blk = blockIdx.x; blk < blocks; blk += gridDim.x) {
   const int64_t row0 = blk * kCmRows + wave * 16;
-  if (pending) {
+  if constexpr (PENDING) {
     const int64_t e = blk * kCmRows + lane;
     if (!__syncthreads_or(wave == 0 && e < N && label_out[e] == kCertPending ? 1 : 0)) continue;
   }
@@ -532,7 +533,7 @@ __global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
   const double n_out = __shfl(nrm, g + 4 * (m16 & 3), kWave);
   if (m16 < 4) {
     const int64_t i = row0 + g + 4 * m16;
-    if (i < N && (!pending || label_out[i] == kCertPending)) {
+    if (i < N && (!PENDING || label_out[i] == kCertPending)) {
       double rv = r[0], mv = v1[0] - v2[0];
       int lab = i1[0];
 #pragma unroll
@@ -549,6 +550,7 @@ __global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
       if (norm2_out) norm2_out[i] = static_cast<float>(n_out);
     }
   }
+  if constexpr (!PENDING) break;
   }
 }
 
@@ -590,18 +592,24 @@ struct MfmaArgs {
   bool pending;
 };
 
-template <bool BF16_STORE, bool TIGHT, int KQ>
-hipError_t launch_mfma_kq(unsigned grid, hipStream_t s, const MfmaArgs& a) {
+template <bool BF16_STORE, bool TIGHT, int KQ, bool PENDING>
+hipError_t launch_mfma_as(unsigned grid, hipStream_t s, const MfmaArgs& a) {
   constexpr size_t lds = static_cast<size_t>(kCmClasses) * (16 * KQ + 4) * sizeof(float);
   if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(certify_mfma_kernel<BF16_STORE, TIGHT, KQ>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(certify_mfma_kernel<BF16_STORE, TIGHT, KQ, PENDING>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((certify_mfma_kernel<BF16_STORE, TIGHT, KQ>), dim3(grid), dim3(kCmThreads), lds, s, a.z, a.N, a.d,
-                     a.W, a.b, a.C, a.sigma, a.row_dist, a.dmax, a.label_out, a.r_out, a.margin_out, a.norm2_out,
-                     a.pending);
+  hipLaunchKernelGGL((certify_mfma_kernel<BF16_STORE, TIGHT, KQ, PENDING>), dim3(grid), dim3(kCmThreads), lds, s, a.z,
+                     a.N, a.d, a.W, a.b, a.C, a.sigma, a.row_dist, a.dmax, a.label_out, a.r_out, a.margin_out,
+                     a.norm2_out);
   return hipGetLastError();
+}
+
+template <bool BF16_STORE, bool TIGHT, int KQ>
+hipError_t launch_mfma_kq(unsigned grid, hipStream_t s, const MfmaArgs& a) {
+  return a.pending ? launch_mfma_as<BF16_STORE, TIGHT, KQ, true>(grid, s, a)
+                   : launch_mfma_as<BF16_STORE, TIGHT, KQ, false>(grid, s, a);
 }
 
 template <bool BF16_STORE, bool TIGHT>
