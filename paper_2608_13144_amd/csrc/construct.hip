@@ -998,15 +998,13 @@ struct CWs {
   uint32_t* ccount;     // [n_classes] candidates, then picks, per class
   int64_t* coff;        // [n_classes + 1] class list offsets
   int64_t* cdst;        // [2 n_classes] output offset and count per class
-  void* sub_ws;  // lookup / insert workspace
+  void* sub_ws;  // lookup workspace
   size_t sub_bytes;
   size_t total;
 };
 
 inline size_t sub_ws_bytes(const lipcache_cache* c) {
-  const size_t a = lipcache_lookup_workspace_bytes(kChunk, c->capacity, c->d, LIPCACHE_F16);
-  const size_t b = lipcache_insert_workspace_bytes(kChunk);
-  return a > b ? a : b;
+  return lipcache_lookup_workspace_bytes(kChunk, c->capacity, c->d, LIPCACHE_F16);
 }
 
 inline CWs cws_layout(int64_t n, int d, int n_classes, int64_t budget, size_t sub_bytes, char* base) {
