@@ -104,3 +104,56 @@ def test_filter_leaves_far_rows_and_heads():
     assert np.array_equal(np.isnan(host(few.r)), np.isnan(host(many.r)[:4000]))
     ref = oracle.certify(z[fine], W, None, sig)
     assert np.array_equal(host(many.label)[fine], ref.label)
+
+
+def check_rows(z, W, store, mode, rows, what):
+    """As check(), with the whole batch on the device and the oracle on `rows` only."""
+    sig = oracle.spectral_norm(W).sigma
+    ref = oracle.certify(z[rows], W, None, sig, store=store, radius_mode=mode)
+    out = api.certify(gpu(z), gpu(W), None, sig, store=store, radius_mode=mode, want_margin=True, want_norm2=True)
+    assert np.array_equal(host(out.label)[rows], ref.label), f"{what}: labels"
+    scale = 1e-13 * np.linalg.norm(z[rows].astype(np.float64), axis=1) * np.linalg.norm(W.astype(np.float64), axis=1).max()
+    apart = np.abs(W.astype(np.float64)[:, None] - W[None]).max(2)
+    for name, tol in (("margin", scale), ("r", scale / min(apart[apart > 0].min(), sig))):
+        got, want = host(getattr(out, name)).astype(np.float64)[rows], getattr(ref, name).astype(np.float64)
+        bad = (np.abs(got - want) > REL * np.abs(want) + tol) & (got != want)
+        assert not bad.any(), f"{what}: {name} {got[bad][:4]} vs {want[bad][:4]}"
+    n2 = ((oracle.bf16_round(z[rows]) if store == "bf16" else z[rows]).astype(np.float64) ** 2).sum(1)
+    assert np.all(np.abs(host(out.norm2)[rows] - n2) <= REL * n2), f"{what}: norms"
+    return ref
+
+
+# the tight radius at every operand width, the narrow ones too (d <= 64 needs
+# more logits than the oracle forms in a test: a sample of the rows)
+@pytest.mark.parametrize("N,d,C,store", [
+    (400033, 32, 64, "f32"), (62503, 64, 200, "bf16"), (192309, 64, 65, "f32"), (63129, 128, 100, "f32"),
+    (15744, 256, 200, "bf16"), (15700, 512, 100, "f32"),
+])
+def test_filter_tight_rows(N, d, C, store):
+    say("certify filter tight rows", N, d, C, store)
+    assert N * C * d >= 8e8
+    rng = np.random.default_rng(N + d + C)
+    W = (rng.standard_normal((C, d)) / math.sqrt(d)).astype(np.float32)
+    mu = 2.0 * rng.standard_normal((C, d))
+    z = (mu[rng.integers(0, C, N)] + 0.8 * rng.standard_normal((N, d))).astype(np.float32)
+    rows = np.unique(np.concatenate([np.arange(200), np.arange(N - 200, N), rng.integers(0, N, 3000)]))
+    check_rows(z, W, store, "tight", rows, f"tight N={N} d={d} C={C} {store}")
+
+
+def test_filter_tight_left_rows_past_the_grid():
+    """The float64 kernel looks for left rows with 2,048 workgroups of 64 rows:
+    past 131,072 rows a workgroup takes a second block.  Left rows in both."""
+    say("certify filter tight, left rows past the grid")
+    rng = np.random.default_rng(11)
+    N, d, C = 180001, 64, 80
+    assert N > 2048 * 64
+    W = (rng.standard_normal((C, d)) / math.sqrt(d)).astype(np.float32)
+    W[1:30] = W[0] + (1e-5 * rng.standard_normal((29, d))).astype(np.float32)
+    W[41] = W[40]
+    z = rng.standard_normal((N, d)).astype(np.float32)
+    left = np.arange(N) % 640 < 5                       # a few blocks in ten, some rows of each
+    z[left] += (6.0 * W[0] / np.linalg.norm(W[0])).astype(np.float32)
+    rows = np.unique(np.concatenate([np.flatnonzero(left), rng.integers(0, N, 1500), np.arange(N - 100, N)]))
+    ref = check_rows(z, W, "f32", "tight", rows, "tight left rows")
+    crowded = np.asarray(ref.label) < 30
+    assert (crowded & (rows > 2048 * 64)).sum() > 200 and (crowded & (rows < 2048 * 64)).sum() > 500
