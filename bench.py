@@ -186,7 +186,8 @@ def stream_bench(args, cfg) -> int:
         dt = time.perf_counter() - ts
         lk = e0.elapsed_time(e1)
         hits = int(res.stats[0].item())
-        rounds.append({"round": t, "n": n_t, "round_ms": dt * 1e3, "lookup_ms": lk, "hits": hits, "inserted": ins})
+        rounds.append({"round": t, "n": n_t, "round_ms": dt * 1e3, "lookup_ms": lk, "hits": hits, "inserted": ins,
+                       "lookup": "prefix scan" if pruned_t else "full contraction"})
         total_s += dt
         total_lk += lk * 1e-3
         flops += 2.0 * B * n_t * (prefix_dims(cache, args) if pruned_t else d)
@@ -194,6 +195,14 @@ def stream_bench(args, cfg) -> int:
     achieved = flops / total_lk / 1e12
     peak = PEAK_TFLOPS[args.precision]
     pairs = sum(B * r["n"] for r in rounds)
+    scans = sum(r["lookup"] == "prefix scan" for r in rounds)
+    scan_dims = prefix_dims(cache, args)
+    how, kernel, formula = {
+        0: ("full contraction + exact re-check", "lookup_dma_kernel", f"2*B*n_t*{d}"),
+        cfg.rounds: ("prefix scan + exact re-check", "lookup_prefix_kernel", f"the prefix contraction 2*B*n_t*{scan_dims}"),
+    }.get(scans, (f"mixed: {scans} of {cfg.rounds} rounds by the prefix scan, the others by the full contraction",
+                  "lookup_prefix_kernel and lookup_dma_kernel",
+                  f"2*B*n_t*{scan_dims} (prefix scan) or 2*B*n_t*{d} (full contraction)"))
     out = {
         "metric": METRIC,
         "value": B * cfg.rounds / total_s,
@@ -210,7 +219,7 @@ def stream_bench(args, cfg) -> int:
         "config": {"workload": cfg.name, "N": N, "B": B, "d": d, "C": C, "store": cfg.store_dtype,
                    "rounds": cfg.rounds, "precision": args.precision,
                    "step": "one round: lookup+certify(B)+insert(misses)",
-                   "lookup": "prefix scan + exact re-check" if pruned_t else "full contraction + exact re-check"},
+                   "lookup": how},
         "pairs_per_s": pairs / total_s,
         "lookup_pairs_per_s": pairs / total_lk,
         "final_n": cache.n,
@@ -218,10 +227,8 @@ def stream_bench(args, cfg) -> int:
         "rounds": rounds,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": None,
-                     "kernel": "lookup_prefix_kernel" if pruned_t else "lookup_dma_kernel",
-                     "algorithmic": (f"sum over rounds of 2*B*n_t*d = {flops:.4e} flop" if not pruned_t else
-                                     f"sum over rounds of the prefix contraction 2*B*n_t*{prefix_dims(cache, args)} = "
-                                     f"{flops:.4e} flop")},
+                     "kernel": kernel,
+                     "algorithmic": f"sum over rounds of {formula} = {flops:.4e} flop"},
         "cpu_baseline": None,
     }
     if not args.no_cpu_baseline:
@@ -665,8 +672,9 @@ def takes_prefix_scan(cache, B, args) -> bool:
     pairs = (B + 511) // 512 * 512 * cache.n
     if args.precision == "f32":
         return cache.store == "f32" and cache.n >= 32768 and pairs * (cache.d - 32) >= 1 << 30
-    large = pairs * (cache.d - (52 if cache.d < 192 else 32)) >= 1 << 33
-    return cache.lookup_prunes("f16") and (args.prune or large)
+    large = (cache.zimg is not None and cache.d >= 64 and cache.n >= 32768
+             and pairs * (cache.d - (52 if cache.d < 192 else 32)) >= 1 << 33)
+    return large or (args.prune and cache.lookup_prunes("f16"))
 
 
 def prefix_dims(cache, args) -> int:
@@ -715,7 +723,7 @@ def full_contraction_context(cache, zq, res, prefix_ms, args) -> dict:
     log(f"full contraction: {ms:.3f} ms ({tflops:.0f} TFLOP/s), same answers: {same}, "
         f"re-checked pairs {sf[1]} (prefix scan {sp[1]})")
     return {"lookup_ms": ms, "lookups_per_s": B / (ms * 1e-3), "tflops": tflops,
-            "frac_of_peak": tflops / PEAK_TFLOPS["f16"], "prefix_scan_speedup": ms / prefix_ms,
+            "frac_of_peak": tflops / PEAK_TFLOPS[args.precision], "prefix_scan_speedup": ms / prefix_ms,
             "same_answers": bool(same), "rechecked_pairs": int(sf[1]), "rechecked_pairs_prefix_scan": int(sp[1])}
 
 
