@@ -73,7 +73,7 @@ enum { LIPCACHE_F32 = 0, LIPCACHE_BF16 = 1, LIPCACHE_F16 = 2 };
  * stats[LIPCACHE_STAT_RECHECKED], which counts fewer pairs the full filter
  * let through that were not hits.  Applies to the float16 filter with
  * 64 <= d <= 512 on caches of n >= 32768 rows with a float16 image (other
- * cases give the same answers with or without it); the workspace grows by
+ * cases do the same with or without it); the workspace grows by
  * about 4 B + 4 n bytes (the entry thresholds padded to a multiple of 1024
  * rows).  A lookup without the option takes the same path by itself when
  * the cache is as above (any d >= 64), the lookup is large enough to gain
@@ -233,14 +233,17 @@ size_t lipcache_lookup_workspace_bytes(int64_t B, int64_t N, int32_t d, int32_t 
 /* 1 if the option LIPCACHE_LOOKUP_PRUNE in `precision` applies to this cache
  * (float16 filter with a float16 image, 64 <= d <= 512, n >= 32768), 0 if
  * it does not, is not set, or an argument is invalid.  (Without the option
- * a large lookup may take the same path: see LIPCACHE_LOOKUP_PRUNE.)  Host
- * only. */
+ * a large lookup takes the same path by itself, and rows of d > 512 always
+ * do on n >= 32768: see LIPCACHE_LOOKUP_PRUNE.)  Host only. */
 int32_t lipcache_lookup_prunes(const lipcache_cache* c, int32_t precision);
 
 /*
  * lipcache_lookup for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same arguments and results as lipcache_lookup without `ws`/`ws_bytes`.
+ * the same arguments and results as lipcache_lookup without `ws`/`ws_bytes`
+ * (the float32 filter always runs the full contraction here, so
+ * stats[LIPCACHE_STAT_RECHECKED] may count more pairs than a lookup that took
+ * the prefix scan).
  * The workspace is a static device array of LIPCACHE_NOALLOC_SCRATCH_BYTES
  * (32 MiB) per GPU, held until the process ends; the call allocates nothing.
  * It serves lookups with lipcache_lookup_workspace_bytes(B, c->n, c->d,

@@ -2163,7 +2163,7 @@ constexpr int64_t kPruneMinRows = 32 * kPrRows;
 //   d = 128 104 - 218 us    88 us       121 us
 //   d = 256  75 -  77 us      -         223 us
 // (1 to 4 pairs in 10,000 pass 16 features of the narrow rows, 2 in 100,000
-// pass 32.)  Where one step is enough at d = 128 it is the faster one (C =
+// pass 32.  Widths between were not measured: 192 is the middle.)  Where one step is enough at d = 128 it is the faster one (C =
 // 100, n = 262,139, B = 16,001: 225 and 336 us, 740 full), but the sizes do
 // not tell these data apart.
 inline int prefix_steps(bool f32, int d) { return f32 || d < 192 ? 2 : 1; }
@@ -2178,6 +2178,15 @@ inline int prefix_steps(bool f32, int d) { return f32 || d < 192 ? 2 : 1; }
 // at n = 65,536 (0.75 2^33), 222 and 197 at n = 262,144; 9x at the headline.
 // The float32 filter spends 12 to 16 times the time per feature: from an
 // eighth of that work on.
+//
+// What the rule cannot see is the data.  With the first 32 features the same in
+// every row and query, so that every slice is handed over after its first tile,
+// it costs (full contraction and default): d = 256, n = 1,048,576, B = 32,768
+// 10.76 and 11.08 ms, B = 16 199 and 309 us; n = 262,144, B = 8,192 755 and 849;
+// d = 512, n = 131,072, B = 4,096 448 and 531; d = 128, n = 262,139, B = 16,001
+// 773 and 917; d = 768, n = 131,072, B = 4,096 3,454 and 3,208; float32, d = 128
+// to 512, 5 to 9%.  The same sizes with features alike: 8.2x, 1.9x, 4.6x, 3.3x,
+// 2.2x, 1.06x and 4.7 to 14x faster.
 inline bool prefix_pays(int32_t precision, int64_t B, int64_t n, int d) {
   const double pairs = static_cast<double>((B + 511) / 512 * 512) * static_cast<double>(n);
   if (precision == LIPCACHE_F32) return pairs * static_cast<double>(d - 32) >= 1073741824.0;
