@@ -4,17 +4,23 @@
 // The margin needs the two largest logits of a row and the tight radius the
 // least (s_y - s_j) / ||W_y - W_j||; which classes those are, float16 matrix
 // instructions (32 times the float64 rate) tell within a rigorous error E:
-//   |s'_c - s_c| <= E = k ||w||_max ||z|| + eta terms + gamma |b|_max
+//   |s'_c - s_c| <= E_c = E_0 + gamma |b_c|, E_0 = k ||w||_max ||z|| + eta terms
 // (k = 2u + u^2 + gamma (1 + u)^2, u = 2^-11; for a bf16 store, exact in
 // float16, k = u + gamma (1 + u); gamma covers four times the float32
-// accumulation, whose order the matrix core does not specify).
+// accumulation, whose order the matrix core does not specify).  E is E_c for
+// the classes that can matter: |b_c| <= |b|_max, and, as b_c = s_c - w_c . z
+// and such a class's s_c is about as large as the row's top two, |b_c| is less
+// than three times M + E_0 + ||w||_max ||z||, M = max(|s'_(1)|, |s'_(2)|); so a
+// class that a bias of -1e9 masks does not widen it.
 //   pass 1  the two largest s' of every row;
 //   pass 2  the classes with s'_c >= s'_(2) - 2E.  Two classes have s >= s'_(2)
 //           - E, so every class of the true top two, ties included, is listed;
 //   exact   float64 sums of the listed classes: label, margin, radius;
 //   tight   pass 3 lists the classes with (s_y - s'_j - E) <= rho ||W_y - W_j||,
 //           rho the exact ratio of the second class, which bounds the minimum
-//           from above, and their exact ratios give the minimum.
+//           from above, and their exact ratios give the minimum.  (Those that
+//           matter have s_j >= s_y - 2 rho ||w||_max, so |b_j| is at most
+//           |s_y| + 2 rho ||w||_max + ||w||_max ||z||.)
 // The numbers that leave are float64 sums as before, of the same values.  Rows
 // that list too many classes (crowded or repeated head rows), lie outside the
 // float16 range or are not finite are left to the float64 kernel.
@@ -255,21 +261,34 @@ __global__ __launch_bounds__(kCfThreads, KS <= 16 ? 3 : 2) void certify_filter_k
     wmax = __builtin_fmaxf(wmax, red[0][w]);
     bmax = __builtin_fmaxf(bmax, red[1][w]);
   }
-  double err;
-  float cut;
-  {
+  // E_0 (returns ||w||_max ||z||), and E where |b_c| <= bound
+  auto row_error = [&](double& e0) {
     constexpr double u = 1.0 / 2048.0, eta = 1.0 / 16384.0;
     const double gam = 4.0 * (d + 2.0) / 16777216.0;
     const double k = BF16_STORE ? u + gam * (1.0 + u) : 2.0 * u + u * u + gam * (1.0 + u) * (1.0 + u);
-    const double wm = static_cast<double>(wmax), bm = static_cast<double>(bmax);
+    const double wm = static_cast<double>(wmax);
     const double zn = __builtin_sqrt(nrm);
-    err = (k * wm * zn + eta * (1.0 + u) * (1.0 + gam) * __builtin_sqrt(static_cast<double>(d)) * (wm + zn) +
-           (1.0 + gam) * d * eta * eta + gam * bm) *
-              (1.0 + 1e-6) +
-          kFilterAbsSlack;
-    if (!(nrm < kF16Range2)) err = __builtin_inf();  // also a NaN row
+    e0 = (k * wm * zn + eta * (1.0 + u) * (1.0 + gam) * __builtin_sqrt(static_cast<double>(d)) * (wm + zn) +
+          (1.0 + gam) * d * eta * eta) *
+             (1.0 + 1e-6) +
+         kFilterAbsSlack;
+    return wm * zn;
+  };
+  auto with_bias = [&](double e0, double bound) {
+    const double gam = 4.0 * (d + 2.0) / 16777216.0;
+    return e0 + gam * __builtin_fmin(static_cast<double>(bmax), bound) * (1.0 + 1e-6);
+  };
+  double err;
+  float cut;
+  {
     const float o1 = __shfl_xor(v1, 32, kWave), o2 = __shfl_xor(v2, 32, kWave);
     v2 = __builtin_fmaxf(__builtin_fminf(v1, o1), __builtin_fmaxf(v2, o2));
+    v1 = __builtin_fmaxf(v1, o1);
+    double e0;
+    const double wz = row_error(e0);
+    const double top = static_cast<double>(__builtin_fmaxf(__builtin_fabsf(v1), __builtin_fabsf(v2)));
+    err = with_bias(e0, 3.0 * (top + e0 + wz));
+    if (!(nrm < kF16Range2)) err = __builtin_inf();  // also a NaN row
     cut = f32_round_down(static_cast<double>(v2) - 2.0 * err);
   }
 
@@ -428,8 +447,11 @@ __global__ __launch_bounds__(kCfThreads, KS <= 16 ? 3 : 2) void certify_filter_k
     const int lab = s_lab[wave][c32];
     const double sy = s_top[wave][c32];
     const float rho = static_cast<float>(s_rho[wave][c32] * (1.0 + 1e-6));
-    const double big = __builtin_fabs(sy) + static_cast<double>(wmax) * __builtin_sqrt(nrm) + static_cast<double>(bmax);
-    const float low = f32_round_down(sy - err - 1e-6 * big);
+    double e0;
+    const double wz = row_error(e0);
+    const double bound = __builtin_fabs(sy) + 2.0 * s_rho[wave][c32] * static_cast<double>(wmax) + wz;
+    const double big = __builtin_fabs(sy) + wz + __builtin_fmin(static_cast<double>(bmax), bound);
+    const float low = f32_round_down(sy - with_bias(e0, bound) - 1e-6 * big);
     const int64_t y = lab < 0 ? 0 : lab;
     n = 0;
     sweep([&](int t, const f32x16& acc) {

@@ -157,3 +157,28 @@ def test_filter_tight_left_rows_past_the_grid():
     ref = check_rows(z, W, "f32", "tight", rows, "tight left rows")
     crowded = np.asarray(ref.label) < 30
     assert (crowded & (rows > 2048 * 64)).sum() > 200 and (crowded & (rows < 2048 * 64)).sum() > 500
+
+
+# masked classes: a large negative bias (it must not reach the error of the
+# others) and an infinite one; large biases throughout, where it does
+@pytest.mark.parametrize("mode", ["conservative", "tight"])
+@pytest.mark.parametrize("mask,spread", [(-1.0e9, 0.1), (-1.0e30, 0.1), (-math.inf, 0.1), (-3.0e3, 300.0)])
+def test_filter_masked_classes(mask, spread, mode):
+    say("certify filter masked classes", mask, spread, mode)
+    rng = np.random.default_rng(12)
+    N, d, C = 63129, 128, 100
+    W = (rng.standard_normal((C, d)) / math.sqrt(d)).astype(np.float32)
+    b = (spread * rng.standard_normal(C)).astype(np.float32)
+    b[::9] = mask
+    z = (2.0 * rng.standard_normal((N, d))).astype(np.float32)
+    rows = np.unique(np.concatenate([np.arange(300), rng.integers(0, N, 2500)]))
+    sig = oracle.spectral_norm(W).sigma
+    ref = oracle.certify(z[rows], W, b, sig, radius_mode=mode)
+    out = api.certify(gpu(z), gpu(W), gpu(b), sig, radius_mode=mode, want_margin=True)
+    assert np.array_equal(host(out.label)[rows], ref.label)
+    # float64 rounding of sums of this size beside one float32 last place
+    tol = 1e-13 * (np.linalg.norm(z[rows].astype(np.float64), axis=1) * 2.0 + 5.0 * spread)
+    for name, t in (("margin", tol), ("r", tol / 0.5)):
+        got, want = host(getattr(out, name)).astype(np.float64)[rows], getattr(ref, name).astype(np.float64)
+        assert np.all(np.abs(got - want) <= REL * np.abs(want) + t), name
+    assert not np.isin(host(out.label)[rows], np.arange(0, C, 9)).any()
