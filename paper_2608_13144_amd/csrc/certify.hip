@@ -328,9 +328,14 @@ __device__ __forceinline__ void stage_head(const float* __restrict__ W, int C, i
 
 // PENDING: a fixed grid looks every block of rows through for labels the
 // filter left (kCertPending), and forms and writes only those; else a
-// workgroup has one block.
+// workgroup has one block.  The loop's registers would cost PENDING a wave per
+// SIMD at some widths, so it states what the other has.
+constexpr int cm_waves(bool tight, int kq, bool pending) {
+  return !pending || kq > 16 ? 1 : kq == 16 ? 2 : kq == 8 ? (tight ? 2 : 3) : tight ? 3 : 4;
+}
+
 template <bool BF16_STORE, bool TIGHT, int KQ, bool PENDING>
-__global__ __launch_bounds__(kCmThreads) void certify_mfma_kernel(
+__global__ __launch_bounds__(kCmThreads, cm_waves(TIGHT, KQ, PENDING)) void certify_mfma_kernel(
     const float* __restrict__ z, int64_t N, int d, const float* __restrict__ W, const float* __restrict__ b, int C,
     double sigma, const double* __restrict__ row_dist, const double* __restrict__ dmax, int32_t* __restrict__ label_out,
     float* __restrict__ r_out, float* __restrict__ margin_out, float* __restrict__ norm2_out) {

@@ -530,7 +530,9 @@ hipError_t launch_filter_d(const float* z, int64_t N, int d, const float* W, con
 // 65,536 (float64 against filter): at N C d = 8.4e8 52.8 and 35.7 us (d = 64, C
 // = 200), 56.7 and 40.6 (128, 100), 62.4 and 54.6 (256, 200), 66.9 and 67.9
 // (512, 100); at half of that 34.2 and 32.8, 35.5 and 40.5, 38.8 and 46.4; at
-// four times it 167 and 64, 253 and 93.  Up to 32 classes (one tile, most of
+// four times it 167 and 64, 253 and 93.  Where every row lists too many classes
+// (200 near copies of one head row, N = 262,144, d = 256) the filter is spent
+// for nothing: 654 and 823 us, tight 900 and 1,159.  Up to 32 classes (one tile, most of
 // it padding for ten) the float64 kernel is near the memory time.
 bool certify_filter_takes(int64_t N, int32_t d, int32_t C) {
   return d <= 512 && C > 32 && C <= 65536 && N < (1ll << 37) &&
